@@ -67,7 +67,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 constexpr TileCfg kTiles[] = {PURO_TILE_LIST(PURO_TILE_ROW)};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 constexpr int kCUs = 256;
-constexpr int kLdsBytes = 160 * 1024;
 
 struct Plan {
     int cfg;             // index into kTiles
@@ -77,8 +76,8 @@ struct Plan {
 
 // Workgroups of a configuration that fit on one CU (by LDS).
 int per_cu(const TileCfg& t, bool grouped) {
-    const int lds = (t.bm + t.bn) * t.sl * t.nst + (grouped ? (t.bm + t.bn) * 4 * t.nst : 0);
-    const int n = kLdsBytes / lds;
+    const int xa = spare_units(t.bm, t.bn, t.sl, t.nst, t.xa, grouped);
+    const int n = kLdsBytes / tile_lds(t.bm, t.bn, t.sl, t.nst, xa, grouped);
     return n < 1 ? 1 : n;
 }
 

@@ -59,6 +59,7 @@ struct TileCfg {
     int bm, bn;          // workgroup tile
     int wm, wn;          // wave grid (wave tile bm/wm x bn/wn)
     int sl, nst;         // k bytes per pipeline slice, ring stages
+    int xa;              // spare 64-row units of the A ring (fewer where LDS lacks room for them)
     int prod;            // producer waves issue the global->LDS loads
     float fixed_us;      // time model: per wave of work units ...
     float slice_us;      // ... plus per k slice of a unit (MI355X, all CUs busy)
@@ -75,11 +76,22 @@ struct TileCfg {
 // time constants are least-squares fits to measured kernel times on the
 // Qwen2-1.5B layer shapes.
 #define PURO_TILE_LIST(X)                                 \
-    X(0, 256, 256, 2, 2, 128, 2, 0, 7.86f, 1.322f)        \
-    X(1, 256, 192, 2, 2, 128, 2, 0, 6.37f, 1.120f)        \
-    X(2, 128, 128, 2, 2, 128, 4, 1, 6.65f, 0.379f)        \
-    X(3, 128, 128, 2, 2, 128, 2, 0, 4.37f, 0.803f)
-#define PURO_TILE_ROW(i, bm, bn, wm, wn, sl, nst, prod, f, s) {bm, bn, wm, wn, sl, nst, prod, f, s},
+    X(0, 256, 256, 2, 2, 128, 2, 4, 0, 7.86f, 1.322f)     \
+    X(1, 256, 192, 2, 2, 128, 2, 4, 0, 6.37f, 1.120f)     \
+    X(2, 128, 128, 2, 2, 128, 4, 0, 1, 6.65f, 0.379f)     \
+    X(3, 128, 128, 2, 2, 128, 2, 0, 0, 4.37f, 0.803f)
+#define PURO_TILE_ROW(i, bm, bn, wm, wn, sl, nst, xa, prod, f, s) {bm, bn, wm, wn, sl, nst, xa, prod, f, s},
+
+constexpr int kLdsBytes = 160 * 1024;
+// LDS bytes of a configuration with xa spare A units, and the spare units
+// that fit (block-scaled operands keep their scales in LDS too).
+constexpr int tile_lds(int bm, int bn, int sl, int nst, int xa, bool grouped) {
+    return (bm + bn) * sl * nst + xa * 64 * sl + (grouped ? (bm + bn) * 4 * nst : 0);
+}
+constexpr int spare_units(int bm, int bn, int sl, int nst, int xa, bool grouped) {
+    return xa > 0 && tile_lds(bm, bn, sl, nst, xa, grouped) > kLdsBytes ? spare_units(bm, bn, sl, nst, xa - 1, grouped)
+                                                                        : xa;
+}
 
 // The bias / residual epilogue: the BF16 bias of columns n..n+3 and the BF16
 // residual of row m at those columns added to four binary32 results (the

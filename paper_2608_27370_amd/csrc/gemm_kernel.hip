@@ -103,25 +103,26 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 }
 
 // Global -> LDS DMA of BYTES (16 or 4) per lane: lane l's data lands at
-// LDS address lds + BYTES * l; offsets at or beyond the descriptor's
-// num_records read as zero. Issued from inline assembly so that the
-// compiler, which cannot tell which LDS bytes a DMA writes, does not make
-// every later LDS read wait for it: the kernel waits explicitly
-// (s_waitcnt vmcnt(0) + barrier) before reading a stage. M0 is saved and
-// restored around the DMA (the compiler may keep a value there), and one wait
-// state separates the M0 write from the DMA that reads it.
+// LDS address lds + BYTES * l; soff (wave-uniform) adds to every lane's
+// offset, and offsets at or beyond the descriptor's num_records read as zero
+// (soff must not exceed num_records: the range check compares voff with
+// num_records - soff). Issued from inline assembly so that the compiler,
+// which cannot tell which LDS bytes a DMA writes, does not make every later
+// LDS read wait for it: the kernel waits explicitly (s_waitcnt vmcnt +
+// barrier) before reading a stage. One wait state separates the M0 write
+// from the DMA that reads it.
 template <int BYTES>
-__device__ __forceinline__ void dma_to_lds(v4i rsrc, uint32_t lds, uint32_t voff) {
+__device__ __forceinline__ void dma_to_lds(v4i rsrc, uint32_t lds, uint32_t voff, uint32_t soff) {
     lds = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds);   // wave-uniform by construction
-    uint32_t saved;
+    soff = (uint32_t)__builtin_amdgcn_readfirstlane((int)soff);
     if constexpr (BYTES == 16)
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                     "buffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-                     : "=&s"(saved) : "s"(lds), "v"(voff), "s"(rsrc) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                     "buffer_load_dwordx4 %1, %2, %3 offen lds"
+                     :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
     else
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                     "buffer_load_dword %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-                     : "=&s"(saved) : "s"(lds), "v"(voff), "s"(rsrc) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                     "buffer_load_dword %1, %2, %3 offen lds"
+                     :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 
 // dz's E4M3 copies from a wave's staged 128 x 128 BF16 tile (row r at
@@ -262,32 +263,46 @@ __device__ __forceinline__ void quantize_staged_dz(const Params& p, const uint8_
 // multiply, so a load that cannot issue (the texture unit's queue full)
 // does not hold up their matrix instructions. Both kinds meet at the one
 // barrier per slice.
-template <int BM, int BN, int WM, int WN, int FA, int FB, int OUT, bool GROUPED, int SL, int NST, bool PROD>
+template <int BM, int BN, int WM, int WN, int FA, int FB, int OUT, bool GROUPED, int SL, int NST, int XA, bool PROD>
 __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel(Params p) {
     constexpr int NW = WM * WN;
     constexpr int WTM = BM / WM, WTN = BN / WN;
     constexpr int FM = WTM / 32, FN = WTN / 32;
     constexpr int KH = SL / 64;                     // 64-byte MFMA k steps per slice
-    constexpr int A_BYTES = BM * SL, B_BYTES = BN * SL;
+    constexpr int A_BYTES = BM * SL, B_BYTES = BN * SL;   // of a slice
     constexpr int STAGE = A_BYTES + B_BYTES;        // one SL-byte k slice of both tiles
-    // 1 KB DMA loads (RPL rows of SL bytes) per wave and slice; when the row
-    // blocks do not divide evenly, the surplus loads repeat earlier blocks
-    // (the same bytes to the same place), so every wave issues the same
-    // number of loads and can wait on an exact count
+    // 1 KB DMA loads (RPL rows of SL bytes) per wave and slice: load q of a
+    // wave brings row block q * NW + wave of its operand
     constexpr int RPL = 1024 / SL;                  // rows per DMA load
     constexpr int CPR = SL / 16;                    // 16-byte chunks per LDS row
     constexpr int A_BLK = BM / RPL, B_BLK = BN / RPL;
-    constexpr int A_PER = (A_BLK + NW - 1) / NW, B_PER = (B_BLK + NW - 1) / NW;
+    constexpr int A_PER = A_BLK / NW, B_PER = B_BLK / NW;
     constexpr int SC_BLK = (BM + BN) / 64;          // 64 scales per 4-byte DMA load
     constexpr int SC_PER = GROUPED ? (SC_BLK + NW - 1) / NW : 0;
     constexpr int LOADS = A_PER + B_PER + SC_PER;
+    // A's ring is counted in units of 64 rows (AU per slice): NST slices and
+    // XA spare units. The spare units take the first XA units of slice
+    // sl + NST while slices sl .. sl + NST - 1 are all still in use, so a
+    // slice's DMA loads spread over both of its k steps (LOADS0 of them in
+    // the first) instead of crowding the second, whose MFMAs they held up.
+    constexpr int AU = BM / 64;
+    constexpr int UNIT = 64 * SL;
+    constexpr int RA = NST * AU + XA;
+    constexpr int LPU = 64 / RPL / NW;              // loads per wave and A unit
+    constexpr int LOADS0 = XA * LPU;
+    constexpr int A_RING = RA * UNIT;
+    constexpr int SMEM = A_RING + NST * B_BYTES;
     static_assert(SL == 64 || SL == 128, "slice width");
-    static_assert(BM % 32 == 0 && BN % 32 == 0 && (BM + BN) % 64 == 0, "tile shape");
-    static_assert(NST >= 2 && (NST - 1) * LOADS <= 63, "pipeline depth");
+    static_assert(BM % 64 == 0 && BN % 32 == 0 && (BM + BN) % 64 == 0, "tile shape");
+    static_assert(A_BLK % NW == 0 && B_BLK % NW == 0 && LPU * NW * RPL == 64 && NW % 2 == 0, "whole loads per wave");
+    static_assert(XA == 0 || (KH == 2 && !PROD && XA <= AU), "spare units");
+    static_assert(NST >= 2 && (NST - 1) * LOADS + LOADS0 <= 63, "pipeline depth");
+    static_assert(WTM % 64 == 0, "a wave's rows are whole A units");
 
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[NST * STAGE];
-    // grouped scales of a slice's rows (A then B), float, DMA'd like the operands
-    __shared__ __attribute__((aligned(16))) float ssc[GROUPED ? NST * (BM + BN) : 1];
+    // A's ring, B's stages, and the grouped scales of a slice's rows (A then
+    // B), float, DMA'd like the operands
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[SMEM + (GROUPED ? NST * (BM + BN) * 4 : 0)];
+    float* const ssc = reinterpret_cast<float*>(smem + SMEM);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -365,13 +380,13 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     // Lane l of a DMA load fills row RPL * blk + l / CPR at position l % CPR,
     // so it fetches the logical chunk (l % CPR) ^ key(row) of that row.
     auto row_key = [](int r) { return SL == 64 ? ((r >> 1) & 3) ^ ((r >> 3) & 1) : (r & 7) ^ ((r >> 3) & 1); };
-    // logical k byte a lane fetches in a load of an even / odd row block
-    const int kch0 = ((lane % CPR) ^ row_key(lane / CPR)) * 16;
-    const int kch1 = ((lane % CPR) ^ row_key(RPL + lane / CPR)) * 16;
-    const uint32_t rowA = (uint32_t)((lane / CPR) * p.lda), rowB = (uint32_t)((lane / CPR) * p.ldb);
+    // logical k byte a lane fetches (a wave's row blocks all have its parity)
+    const int kch = ((lane % CPR) ^ row_key((wave & 1) * RPL + lane / CPR)) * 16;
     const uint32_t blkA = (uint32_t)(RPL * p.lda), blkB = (uint32_t)(RPL * p.ldb);
+    const uint32_t voffA = (uint32_t)((lane / CPR) * p.lda) + wave * blkA + kch;
+    const uint32_t voffB = (uint32_t)((lane / CPR) * p.ldb) + wave * blkB + kch;
     const uint32_t smem_lds = lds_addr(smem);
-    const uint32_t ssc_lds = lds_addr(ssc);
+    const uint32_t ssc_lds = smem_lds + SMEM;
 
     v4i rsa{}, rsb{};
     // Scale load j of this wave brings entries 64 t .. 64 t + 63 (t = its
@@ -412,29 +427,31 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     }
     (void)sc_base; (void)sc_kstride; (void)sc_is_a;
 
-    // DMA load q (0 <= q < LOADS) of this wave for slice `sl` into ring
-    // stage `st`. With `valid` false the load still issues (so that every
-    // wave always has the same number in flight and waits on constant
-    // counts) but reads out of range: no memory traffic, zeros into a stage
-    // no later slice uses.
-    auto dma_one = [&](int st, int sl, int q, bool valid) __attribute__((always_inline)) {
+    auto wrap = [](int u) __attribute__((always_inline)) { return u >= RA ? u - RA : u; };
+    // DMA load q (0 <= q < LOADS) of this wave for slice `sl`: A's into the
+    // ring units from ua (that slice's first), the rest into stage `st`. With
+    // `valid` false the load still issues (so that every wave always has the
+    // same number in flight and waits on constant counts) but reads out of
+    // range: no memory traffic, zeros into a place no later slice uses.
+    auto dma_one = [&](int ua, int st, int sl, int q, bool valid) __attribute__((always_inline)) {
         const int k0 = sl * SL;
-        const uint32_t sbase = smem_lds + st * STAGE;
         if (q < A_PER + B_PER) {
-            const bool is_a = q < A_PER;
-            const int blk = is_a ? (wave * A_PER + q) % A_BLK : (wave * B_PER + (q - A_PER)) % B_BLK;
-            const int kch = (blk & 1) ? kch1 : kch0;
             // the k tail (K % SL != 0) also reads out of range on purpose: zeros
-            const uint32_t off = (valid && k0 + kch < p.K) ? (uint32_t)(k0 + kch) : kOOB;
-            if (is_a) dma_to_lds<16>(ra, sbase + blk * 1024, rowA + blk * blkA + off);
-            else dma_to_lds<16>(rb, sbase + A_BYTES + blk * 1024, rowB + blk * blkB + off);
+            const bool in = valid && k0 + kch < p.K;
+            const uint32_t soff = valid ? (uint32_t)k0 : 0u;
+            if (q < A_PER)
+                dma_to_lds<16>(ra, smem_lds + wrap(ua + q / LPU) * UNIT + (q % LPU) * (NW * 1024) + wave * 1024,
+                               (in ? voffA : kOOB) + q * (NW * blkA), soff);
+            else
+                dma_to_lds<16>(rb, smem_lds + A_RING + st * B_BYTES + (q - A_PER) * (NW * 1024) + wave * 1024,
+                               (in ? voffB : kOOB) + (q - A_PER) * (NW * blkB), soff);
         } else if constexpr (GROUPED) {
             const int j = q - A_PER - B_PER;
             const int t = (wave * SC_PER + j) % SC_BLK;
             const int kb = sl / SPB;
             const uint32_t soff = (valid && sc_base[j] >= 0) ? (uint32_t)(sc_base[j] + kb * sc_kstride[j]) * 4u : kOOB;
             const uint32_t dst = ssc_lds + (st * (BM + BN) + t * 64) * 4;
-            dma_to_lds<4>(sc_is_a[j] ? rsa : rsb, dst, soff);
+            dma_to_lds<4>(sc_is_a[j] ? rsa : rsb, dst, soff, 0u);
         }
     };
 
@@ -479,10 +496,10 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     // scales_e8m0 turns them into the instruction's operands once they have
     // landed, so that no read waits on its own result)
     constexpr int NPIECE = (FM + FN) * (GROUPED ? 2 : 1);
-    auto read_piece = [&](Frags& f, int st, int h, int t) __attribute__((always_inline)) {
+    auto read_piece = [&](Frags& f, int ua, int st, int h, int t) __attribute__((always_inline)) {
         if (t < FM + FN) {
-            const uint8_t* row = t < FM ? smem + st * STAGE + (wm * WTM + t * 32 + fr) * SL
-                                        : smem + st * STAGE + A_BYTES + (wn * WTN + (t - FM) * 32 + fr) * SL;
+            const uint8_t* row = t < FM ? smem + wrap(ua + wm * (WTM / 64) + t / 2) * UNIT + ((t % 2) * 32 + fr) * SL
+                                        : smem + A_RING + st * B_BYTES + (wn * WTN + (t - FM) * 32 + fr) * SL;
             const int cc = 4 * h + c0;
             const v4i lo = *reinterpret_cast<const v4i*>(row + ((cc ^ key) << 4));
             const v4i hi = *reinterpret_cast<const v4i*>(row + (((cc + 1) ^ key) << 4));
@@ -537,18 +554,22 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     // fetch stale LDS data that is never used, and DMA loads past it read
     // nothing.
     constexpr int NMFMA = FM * FN;
-    auto step = [&](int sl, int h, Frags& cur, Frags& nxt) __attribute__((always_inline)) {
+    auto step = [&](int sl, int ua, int h, Frags& cur, Frags& nxt) __attribute__((always_inline)) {
         const bool last = h == KH - 1;
         if (last) {
             if constexpr (PROD)
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             else
-                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((NST - 2) * LOADS) : "memory");
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((NST - 2) * LOADS + LOADS0) : "memory");
             __syncthreads();
         }
         const int st = (sl - s0) % NST;
         const int rst = last ? (sl + 1 - s0) % NST : st;   // stage and k step read into nxt
         const int rh = last ? 0 : h + 1;
+        const int rua = last ? wrap(ua + AU) : ua;
+        // the ring unit at which slice sl + NST starts: XA units before
+        // slice sl's first (NST AU = RA - XA units on)
+        const int dua = XA ? (ua >= XA ? ua - XA : ua - XA + RA) : ua;
         const bool refill = sl + NST < s1;
         // fragment read u goes after MFMA u * NMFMA / NPIECE (the first half
         // of the step), DMA load q after MFMA q * NMFMA / LOADS (constant loop
@@ -568,16 +589,18 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
             mfma_one(cur, t);
 #pragma unroll
             for (int u = 0; u < FM + FN; ++u)
-                if (u * NMFMA / NPIECE == t) read_piece(nxt, rst, rh, u);
+                if (u * NMFMA / NPIECE == t) read_piece(nxt, rua, rst, rh, u);
             if (last) {
 #pragma unroll
                 for (int u = FM + FN; u < NPIECE; ++u)
-                    if (NMFMA / 2 + (u - FM - FN) / 2 == t) read_piece(nxt, rst, rh, u);
+                    if (NMFMA / 2 + (u - FM - FN) / 2 == t) read_piece(nxt, rua, rst, rh, u);
             }
-            if (last && !PROD) {
+            if (!PROD) {
+                constexpr int L1 = LOADS - LOADS0;
 #pragma unroll
-                for (int q = 0; q < LOADS; ++q)
-                    if (q * NMFMA / LOADS == t) dma_one(st, sl + NST, q, refill);
+                for (int q = 0; q < (last ? L1 : LOADS0); ++q)
+                    if (q * NMFMA / (last ? L1 : LOADS0 ? LOADS0 : 1) == t)
+                        dma_one(dua, st, sl + NST, last ? LOADS0 + q : q, refill);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -589,7 +612,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
 #pragma unroll
         for (int t = 0; t < NST; ++t)
 #pragma unroll
-            for (int q = 0; q < LOADS; ++q) dma_one(t, s0 + t, q, s0 + t < s1);
+            for (int q = 0; q < LOADS; ++q) dma_one(t * AU, t, s0 + t, q, s0 + t < s1);
         asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NST - 1) * LOADS) : "memory");
     }
     __syncthreads();
@@ -604,7 +627,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
                 __syncthreads();
                 const int st = (sl - s0) % NST;
 #pragma unroll
-                for (int q = 0; q < LOADS; ++q) dma_one(st, sl + NST, q, sl + NST < s1);
+                for (int q = 0; q < LOADS; ++q) dma_one(st * AU, st, sl + NST, q, sl + NST < s1);
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();   // the epilogue's barrier: the ring is idle
@@ -613,20 +636,24 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     }
     Frags F0, F1;
 #pragma unroll
-    for (int t = 0; t < NPIECE; ++t) read_piece(F0, 0, 0, t);
+    for (int t = 0; t < NPIECE; ++t) read_piece(F0, 0, 0, 0, t);
     scales_e8m0(F0);
+    int ua = 0;                                // slice sl's first unit in A's ring
     if constexpr (KH == 2) {
         for (int sl = s0; sl < s1; ++sl) {
-            step(sl, 0, F0, F1);
-            step(sl, 1, F1, F0);
+            step(sl, ua, 0, F0, F1);
+            step(sl, ua, 1, F1, F0);
+            ua = wrap(ua + AU);
         }
     } else {
         int sl = s0;
         for (; sl + 1 < s1; sl += 2) {
-            step(sl, 0, F0, F1);
-            step(sl + 1, 0, F1, F0);
+            step(sl, ua, 0, F0, F1);
+            ua = wrap(ua + AU);
+            step(sl + 1, ua, 0, F1, F0);
+            ua = wrap(ua + AU);
         }
-        if (sl < s1) step(sl, 0, F0, F1);
+        if (sl < s1) step(sl, ua, 0, F0, F1);
     }
     // the loads issued for slices past the end write zeros into the ring,
     // which the epilogue reuses: let them land first
@@ -814,7 +841,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
 #pragma unroll
                     for (int q = 0; q < WTM / 4; ++q) {          // 1 KB: four rows of 256 bytes
                         const int r = q * 4 + (lane >> 4), c = (lane & 15) ^ (r & 15);
-                        dma_to_lds<16>(rr, ep_lds + q * 1024, (uint32_t)((r * p.ldr + c * 8) * 2));
+                        dma_to_lds<16>(rr, ep_lds + q * 1024, (uint32_t)((r * p.ldr + c * 8) * 2), 0u);
                     }
                 }
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1158,39 +1185,39 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     });
 }
 
-template <int BM, int BN, int WM, int WN, int SL, int NST, int PROD, int FA, int FB, bool GROUPED, int OUT>
+template <int BM, int BN, int WM, int WN, int SL, int NST, int XA, int PROD, int FA, int FB, bool GROUPED, int OUT>
 void launch_cfg(const Params& prm, int grid, hipStream_t stream) {
     constexpr int threads = WM * WN * 64 * (PROD ? 2 : 1);
-    gemm_fp8_kernel<BM, BN, WM, WN, FA, FB, OUT, GROUPED, SL, NST, PROD != 0><<<grid, threads, 0, stream>>>(prm);
+    gemm_fp8_kernel<BM, BN, WM, WN, FA, FB, OUT, GROUPED, SL, NST, spare_units(BM, BN, SL, NST, XA, GROUPED), PROD != 0><<<grid, threads, 0, stream>>>(prm);
 }
 
-template <int BM, int BN, int WM, int WN, int SL, int NST, int PROD, int FA, int FB, bool GROUPED>
+template <int BM, int BN, int WM, int WN, int SL, int NST, int XA, int PROD, int FA, int FB, bool GROUPED>
 void launch_tile(const Params& prm, int out, int grid, hipStream_t stream) {
     // the LM-head kinds exist for BF16 operands and blockwise E4M3 operands,
     // on 128-column wave tiles
     constexpr bool lm = (FA == kBF16 && FB == kBF16 && !GROUPED) || (FA == kE4M3 && FB == kE4M3 && GROUPED);
-    if (out == 2) launch_cfg<BM, BN, WM, WN, SL, NST, PROD, FA, FB, GROUPED, 2>(prm, grid, stream);
-    else if (out == kOutF32) launch_cfg<BM, BN, WM, WN, SL, NST, PROD, FA, FB, GROUPED, kOutF32>(prm, grid, stream);
+    if (out == 2) launch_cfg<BM, BN, WM, WN, SL, NST, XA, PROD, FA, FB, GROUPED, 2>(prm, grid, stream);
+    else if (out == kOutF32) launch_cfg<BM, BN, WM, WN, SL, NST, XA, PROD, FA, FB, GROUPED, kOutF32>(prm, grid, stream);
     else if (out == kOutBF16Epi)
-        launch_cfg<BM, BN, WM, WN, SL, NST, PROD, FA, FB, GROUPED, kOutBF16Epi>(prm, grid, stream);
+        launch_cfg<BM, BN, WM, WN, SL, NST, XA, PROD, FA, FB, GROUPED, kOutBF16Epi>(prm, grid, stream);
     else if (out == kOutLseStats || out == kOutSoftmaxGrad) {
         if constexpr (lm && BN / WN == 128) {
-            if (out == kOutLseStats) launch_cfg<BM, BN, WM, WN, SL, NST, PROD, FA, FB, GROUPED, kOutLseStats>(prm, grid, stream);
-            else launch_cfg<BM, BN, WM, WN, SL, NST, PROD, FA, FB, GROUPED, kOutSoftmaxGrad>(prm, grid, stream);
+            if (out == kOutLseStats) launch_cfg<BM, BN, WM, WN, SL, NST, XA, PROD, FA, FB, GROUPED, kOutLseStats>(prm, grid, stream);
+            else launch_cfg<BM, BN, WM, WN, SL, NST, XA, PROD, FA, FB, GROUPED, kOutSoftmaxGrad>(prm, grid, stream);
         }
     } else if (out == kOutSoftmaxGradQ) {
         // the blockwise E4M3 recipe's backward, 128 x 128 wave tiles
         if constexpr (FA == kE4M3 && FB == kE4M3 && GROUPED && BM / WM == 128 && BN / WN == 128)
-            launch_cfg<BM, BN, WM, WN, SL, NST, PROD, FA, FB, GROUPED, kOutSoftmaxGradQ>(prm, grid, stream);
-    } else launch_cfg<BM, BN, WM, WN, SL, NST, PROD, FA, FB, GROUPED, kOutBF16>(prm, grid, stream);
+            launch_cfg<BM, BN, WM, WN, SL, NST, XA, PROD, FA, FB, GROUPED, kOutSoftmaxGradQ>(prm, grid, stream);
+    } else launch_cfg<BM, BN, WM, WN, SL, NST, XA, PROD, FA, FB, GROUPED, kOutBF16>(prm, grid, stream);
 }
 
 }  // namespace
 
 template <int FA, int FB, bool GROUPED>
 void launch_variant(const Params& prm, int cfg, int out, int grid, hipStream_t stream) {
-#define PURO_TILE_CASE(i, bm, bn, wm, wn, sl, nst, prod, f, s) \
-    case i: launch_tile<bm, bn, wm, wn, sl, nst, prod, FA, FB, GROUPED>(prm, out, grid, stream); break;
+#define PURO_TILE_CASE(i, bm, bn, wm, wn, sl, nst, xa, prod, f, s) \
+    case i: launch_tile<bm, bn, wm, wn, sl, nst, xa, prod, FA, FB, GROUPED>(prm, out, grid, stream); break;
     switch (cfg) { PURO_TILE_LIST(PURO_TILE_CASE) }
 #undef PURO_TILE_CASE
 }
