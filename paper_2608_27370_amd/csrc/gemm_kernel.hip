@@ -97,6 +97,13 @@ __device__ __forceinline__ v4i make_rsrc(const void* base, uint32_t bytes) {
     return r;
 }
 
+// Arithmetic on the wave-uniform x stays behind this point (the empty asm
+// takes and gives x; the compiler moves neither it nor what uses x after it).
+__device__ __forceinline__ void pin(int& x) {
+    x = __builtin_amdgcn_readfirstlane(x);
+    asm volatile("" : "+s"(x));
+}
+
 // LDS byte address of a __shared__ object (the value M0 takes for a DMA).
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)p;
@@ -135,7 +142,8 @@ __device__ __forceinline__ void dma_to_lds(v4i rsrc, uint32_t lds, uint32_t voff
 //    of 8 rows b = (l >> 4) + 4 k; the 4 lanes of a chunk share the column
 //    maxima through two shuffles, each 8 x 8 block is transposed in
 //    registers and its 8 columns' codes go to the transposed copy.
-__device__ __forceinline__ void quantize_staged_dz(const Params& p, const uint8_t* ep, int64_t mrow0, int64_t ncol0,
+template <class P>
+__device__ __forceinline__ void quantize_staged_dz(const P& p, const uint8_t* ep, int64_t mrow0, int64_t ncol0,
                                                    int lane) {
     typedef unsigned int v4u __attribute__((ext_vector_type(4)));
     constexpr int F = kE4M3;
@@ -292,7 +300,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     constexpr int LOADS0 = XA * LPU;
     constexpr int A_RING = RA * UNIT;
     constexpr int SMEM = A_RING + NST * B_BYTES;
-    static_assert(SL == 64 || SL == 128, "slice width");
+    static_assert(SL == kBK, "a slice is one k block");
     static_assert(BM % 64 == 0 && BN % 32 == 0 && (BM + BN) % 64 == 0, "tile shape");
     static_assert(A_BLK % NW == 0 && B_BLK % NW == 0 && LPU * NW * RPL == 64 && NW % 2 == 0, "whole loads per wave");
     static_assert(XA == 0 || (KH == 2 && !PROD && XA <= AU), "spare units");
@@ -356,10 +364,9 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
         if (p.a_mode == kSTensor) alpha *= p.sa[0];
         if (p.b_mode == kSTensor) alpha *= p.sb[0];
     }
-    // k slices [s0, s1) of SL bytes: this split's 128-wide k blocks
-    constexpr int SPB = kBK / SL;                   // slices per 128-wide k block
-    const int s0 = SPB * ks * p.ksteps_per_split;
-    const int s1 = SPB * min((ks + 1) * p.ksteps_per_split, p.ksteps);
+    // k slices [s0, s1): this split's 128-byte k blocks
+    const int s0 = ks * p.ksteps_per_split;
+    const int s1 = min((ks + 1) * p.ksteps_per_split, p.ksteps);
 
     const int valid_m = min(BM, p.M - m0), valid_n = min(BN, p.N - n0);
     const v4i ra = make_rsrc(p.A + (int64_t)m0 * p.lda, (uint32_t)(valid_m * p.lda));
@@ -379,7 +386,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     //    128-byte line get the keys 0..7.
     // Lane l of a DMA load fills row RPL * blk + l / CPR at position l % CPR,
     // so it fetches the logical chunk (l % CPR) ^ key(row) of that row.
-    auto row_key = [](int r) { return SL == 64 ? ((r >> 1) & 3) ^ ((r >> 3) & 1) : (r & 7) ^ ((r >> 3) & 1); };
+    auto row_key = [](int r) { return (r & 7) ^ ((r >> 3) & 1); };
     // logical k byte a lane fetches (a wave's row blocks all have its parity)
     const int kch = ((lane % CPR) ^ row_key((wave & 1) * RPL + lane / CPR)) * 16;
     const uint32_t blkA = (uint32_t)(RPL * p.lda), blkB = (uint32_t)(RPL * p.ldb);
@@ -392,11 +399,12 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     // Scale load j of this wave brings entries 64 t .. 64 t + 63 (t = its
     // chunk) of a slice's scale vector: BM entries for A, then BN for B. A
     // row-scaled operand has one entry per tile row, a block-scaled one one
-    // per 128-row block (entries past that are unused). The element lane l
-    // loads for k block kb is sc_base[j] + kb * sc_kstride[j] (row-major
-    // scales: stride 1; k-major: the array's row pitch), or nothing when
-    // sc_base[j] < 0; all of it is fixed before the main loop.
-    int sc_base[SC_PER > 0 ? SC_PER : 1], sc_kstride[SC_PER > 0 ? SC_PER : 1];
+    // per 128-row block (entries past that are unused). Lane l loads the
+    // element at byte sc_base[j] + kb * sc_kstride[j] for k block kb
+    // (row-major scales: a stride of one element; k-major: the array's row
+    // pitch), or nothing when sc_base[j] is kOOB; all of it is fixed before
+    // the main loop.
+    uint32_t sc_base[SC_PER > 0 ? SC_PER : 1], sc_kstride[SC_PER > 0 ? SC_PER : 1];
     bool sc_is_a[SC_PER > 0 ? SC_PER : 1];
     if constexpr (GROUPED) {
         rsa = make_rsrc(p.sa, p.a_mode == kSTensor ? 0u : p.sa_bytes);
@@ -421,37 +429,46 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
                 if (row0 + r < rows) unit = row0 + r;
             }
             sc_is_a[j] = is_a;
-            sc_base[j] = unit < 0 ? -1 : (km ? unit : unit * ld);
-            sc_kstride[j] = km ? ld : 1;
+            sc_base[j] = unit < 0 ? kOOB : (uint32_t)(km ? unit : unit * ld) * 4u;
+            // (no stride without scales: an empty descriptor takes no offset)
+            sc_kstride[j] = mode == kSTensor ? 0u : (km ? (uint32_t)ld : 1u) * 4u;
         }
     }
     (void)sc_base; (void)sc_kstride; (void)sc_is_a;
 
-    auto wrap = [](int u) __attribute__((always_inline)) { return u >= RA ? u - RA : u; };
-    // DMA load q (0 <= q < LOADS) of this wave for slice `sl`: A's into the
-    // ring units from ua (that slice's first), the rest into stage `st`. With
-    // `valid` false the load still issues (so that every wave always has the
-    // same number in flight and waits on constant counts) but reads out of
-    // range: no memory traffic, zeros into a place no later slice uses.
-    auto dma_one = [&](int ua, int st, int sl, int q, bool valid) __attribute__((always_inline)) {
+    // positions in A's ring, bytes
+    auto wrap = [](int u) __attribute__((always_inline)) { return u >= A_RING ? u - A_RING : u; };
+    // What the DMA loads of slice `sl` share: the lane offsets into A and B
+    // (out of range in the k tail, K % SL != 0, which reads as zeros on
+    // purpose), the k offset, and where the slice starts in A's ring. Past
+    // the last slice (!valid) the loads still issue, so that every wave
+    // always has the same number in flight and waits on constant counts, but
+    // read out of range: no memory traffic, zeros into a place no later slice
+    // uses.
+    struct Slice {
+        uint32_t va, vb, soff;
+        int ua;
+        bool valid;
+    };
+    auto slice_loads = [&](int ua, int sl, bool valid) __attribute__((always_inline)) {
         const int k0 = sl * SL;
-        if (q < A_PER + B_PER) {
-            // the k tail (K % SL != 0) also reads out of range on purpose: zeros
-            const bool in = valid && k0 + kch < p.K;
-            const uint32_t soff = valid ? (uint32_t)k0 : 0u;
-            if (q < A_PER)
-                dma_to_lds<16>(ra, smem_lds + wrap(ua + q / LPU) * UNIT + (q % LPU) * (NW * 1024) + wave * 1024,
-                               (in ? voffA : kOOB) + q * (NW * blkA), soff);
-            else
-                dma_to_lds<16>(rb, smem_lds + A_RING + st * B_BYTES + (q - A_PER) * (NW * 1024) + wave * 1024,
-                               (in ? voffB : kOOB) + (q - A_PER) * (NW * blkB), soff);
+        const bool in = k0 + kch < (valid ? p.K : 0);
+        return Slice{in ? voffA : kOOB, in ? voffB : kOOB, valid ? (uint32_t)k0 : 0u, ua, valid};
+    };
+    // DMA load q (0 <= q < LOADS) of this wave: A's into the ring, the rest
+    // into stage `st`.
+    auto dma_one = [&](const Slice& s, int st, int q) __attribute__((always_inline)) {
+        if (q < A_PER) {
+            dma_to_lds<16>(ra, smem_lds + wrap(s.ua + q / LPU * UNIT) + (q % LPU) * (NW * 1024) + wave * 1024,
+                           s.va + q * (NW * blkA), s.soff);
+        } else if (q < A_PER + B_PER) {
+            dma_to_lds<16>(rb, smem_lds + A_RING + st * B_BYTES + (q - A_PER) * (NW * 1024) + wave * 1024,
+                           s.vb + (q - A_PER) * (NW * blkB), s.soff);
         } else if constexpr (GROUPED) {
             const int j = q - A_PER - B_PER;
             const int t = (wave * SC_PER + j) % SC_BLK;
-            const int kb = sl / SPB;
-            const uint32_t soff = (valid && sc_base[j] >= 0) ? (uint32_t)(sc_base[j] + kb * sc_kstride[j]) * 4u : kOOB;
             const uint32_t dst = ssc_lds + (st * (BM + BN) + t * 64) * 4;
-            dma_to_lds<4>(sc_is_a[j] ? rsa : rsb, dst, soff, 0u);
+            dma_to_lds<4>(sc_is_a[j] ? rsa : rsb, dst, s.valid ? sc_base[j] : kOOB, (s.soff / kBK) * sc_kstride[j]);
         }
     };
 
@@ -479,9 +496,8 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     // the LDS entry of each fragment row's scale within a stage's scale
     // vector (block scales: the row's 128-row block counted from the block
     // of the tile's first row, which need not start a block when the tile
-    // is 192 rows), and whether the operand has grouped scales at all
+    // is 192 rows)
     int sc_off[FM + FN];
-    bool sc_on[FM + FN];
 #pragma unroll
     for (int fi = 0; fi < FM + FN; ++fi) {
         const bool is_a = fi < FM;
@@ -489,32 +505,57 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
         const int row0 = is_a ? m0 : n0;
         const int mode = is_a ? p.a_mode : p.b_mode;
         sc_off[fi] = (is_a ? 0 : BM) + (mode == kSBlock ? ((row0 + r) >> 7) - (row0 >> 7) : r);
-        sc_on[fi] = mode != kSTensor;
     }
     // read piece t of k step h of the slice in stage st: t < FM + FN are
     // the operand fragments, the rest the scales (their raw binary32 bits:
-    // scales_e8m0 turns them into the instruction's operands once they have
+    // scale_e8m0 turns them into the instruction's operands once they have
     // landed, so that no read waits on its own result)
+    // (LDS addresses: `at` holds a lane's two 16-byte chunks of the k step in
+    // each of its A units' first fragment row, then in B's)
     constexpr int NPIECE = (FM + FN) * (GROUPED ? 2 : 1);
-    auto read_piece = [&](Frags& f, int ua, int st, int h, int t) __attribute__((always_inline)) {
+    constexpr int UW = WTM / 64;                 // A units of a wave
+    struct Addr {
+        uint32_t lo[UW + 1], hi[UW + 1];
+    };
+    typedef const __attribute__((address_space(3))) v4i* lds_v4i;
+    uint32_t lane_at[KH][2];
+#pragma unroll
+    for (int h = 0; h < KH; ++h)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) lane_at[h][c] = smem_lds + fr * SL + (((4 * h + c0 + c) ^ key) << 4);
+    auto address = [&](int ua, int st, int h) __attribute__((always_inline)) {
+        Addr at;
+#pragma unroll
+        for (int u = 0; u <= UW; ++u) {
+            const uint32_t off = u < UW ? wrap(ua + (wm * UW + u) * UNIT) : A_RING + st * B_BYTES + wn * WTN * SL;
+            at.lo[u] = lane_at[h][0] + off;
+            at.hi[u] = lane_at[h][1] + off;
+        }
+        return at;
+    };
+    auto read_piece = [&](Frags& f, const Addr& at, int st, int t) __attribute__((always_inline)) {
         if (t < FM + FN) {
-            const uint8_t* row = t < FM ? smem + wrap(ua + wm * (WTM / 64) + t / 2) * UNIT + ((t % 2) * 32 + fr) * SL
-                                        : smem + A_RING + st * B_BYTES + (wn * WTN + (t - FM) * 32 + fr) * SL;
-            const int cc = 4 * h + c0;
-            const v4i lo = *reinterpret_cast<const v4i*>(row + ((cc ^ key) << 4));
-            const v4i hi = *reinterpret_cast<const v4i*>(row + (((cc + 1) ^ key) << 4));
+            const int u = t < FM ? t / 2 : UW, off = (t < FM ? t % 2 : t - FM) * (32 * SL);
+            const v4i lo = *(lds_v4i)(uintptr_t)(at.lo[u] + off);
+            const v4i hi = *(lds_v4i)(uintptr_t)(at.hi[u] + off);
             f.f[t] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         } else {
             const int fi = t - (FM + FN);
             f.sc[fi] = __float_as_uint(ssc[st * (BM + BN) + sc_off[fi]]);
         }
     };
-    // the E8M0 exponent of each scale (127, a factor of 1, for a per-tensor
-    // scaled operand, whose factor the epilogue applies)
-    auto scales_e8m0 = [&](Frags& f) __attribute__((always_inline)) {
+    // The matrix instruction's scale operand of fragment fi: the E8M0
+    // exponent in the top byte (the instruction takes byte 3; the bits below
+    // it are ignored), 127 (a factor of 1) for a per-tensor scaled operand,
+    // whose LDS entries are zeros and whose factor the epilogue applies. The
+    // empty asm keeps the shift here: the compiler would otherwise place it
+    // at the LDS read and wait for that read at once.
+    const uint32_t unit_a = p.a_mode == kSTensor ? 127u << 24 : 0u;
+    const uint32_t unit_b = p.b_mode == kSTensor ? 127u << 24 : 0u;
+    auto scale_e8m0 = [&](Frags& f, int fi) __attribute__((always_inline)) {
         if constexpr (GROUPED) {
-#pragma unroll
-            for (int fi = 0; fi < FM + FN; ++fi) f.sc[fi] = sc_on[fi] ? (f.sc[fi] >> 23) & 0xFFu : 127u;
+            asm volatile("" : "+v"(f.sc[fi]));
+            f.sc[fi] = (f.sc[fi] << 1) | (fi < FM ? unit_a : unit_b);
         }
     };
     auto mfma_one = [&](const Frags& f, int t) __attribute__((always_inline)) {
@@ -533,7 +574,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
                                                                 __builtin_bit_cast(v8bf, ahi), acc[i][j], 0, 0, 0);
         } else if constexpr (GROUPED)
             acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                f.f[FM + j], f.f[i], acc[i][j], FB, FA, 0, (int)f.sc[FM + j], 0, (int)f.sc[i]);
+                f.f[FM + j], f.f[i], acc[i][j], FB, FA, 3, (int)f.sc[FM + j], 3, (int)f.sc[i]);
         else
             acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
                 f.f[FM + j], f.f[i], acc[i][j], FB, FA, 0, 127, 0, 127);
@@ -541,70 +582,92 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
 
     // One pipeline step: the MFMAs of k step h of slice sl (fragments in
     // `cur`, read during the previous step) with the LDS reads of the next
-    // k step (into `nxt`) and, in a slice's last k step, the DMA loads of
-    // slice sl + NST interleaved between them, so that LDS and memory
-    // latency hide behind the MFMAs.
+    // k step (into `nxt`, from `at`) and DMA loads of slice sl + NST
+    // interleaved between them, so that LDS and memory latency hide behind
+    // the MFMAs: the loads into A's spare units in the first k step, the rest
+    // in the last.
     // Before the reads of the next slice (in its last k step) a wave waits
-    // until at most NST - 2 slices of its DMA loads remain in flight (every
-    // wave always has NST - 1 in flight then, so its loads of slice sl + 1
-    // have landed) and until its reads of slice sl are complete
-    // (lgkmcnt(0)). After the barrier every wave is at that point: slice
-    // sl + 1 is in LDS and the stage of slice sl is free for the DMA of slice
-    // sl + NST. The loop body has no branches: reads past the last slice
-    // fetch stale LDS data that is never used, and DMA loads past it read
-    // nothing.
+    // until its loads of slice sl + 1 have landed (the NST - 2 slices after
+    // it and the LOADS0 loads just issued may still be in flight) and until
+    // its reads of slice sl are complete (lgkmcnt(0)). After the barrier
+    // every wave is at that point: slice sl + 1 is in LDS and the places of
+    // slice sl are free for the DMA of slice sl + NST. The loop body has no
+    // branches: reads past the last slice fetch stale LDS data that is never
+    // used, and DMA loads past it read nothing.
+    // Everything but the MFMAs has to fit into the 16 issue slots an MFMA
+    // leaves its wave: the wait and the barrier come after the step's first
+    // MFMA (which needs only registers), the DMA loads' shared state after
+    // the second, the next step's read addresses three before the last. Empty
+    // asm statements keep the compiler from moving that arithmetic (pin) or
+    // the MFMAs themselves ("+a").
     constexpr int NMFMA = FM * FN;
-    auto step = [&](int sl, int ua, int h, Frags& cur, Frags& nxt) __attribute__((always_inline)) {
+    constexpr int SC0 = NMFMA / 2, SCD = NMFMA / 4;
+    constexpr int TAT = NMFMA > 4 ? NMFMA - 3 : 2;
+    int ua = 0, st = 0;                        // where slice sl starts in A's ring, its stage
+    int un = 0, stn = 0;                       // the same of slice sl + 1
+    Slice ld{};
+    auto step = [&](int sl, int h, Frags& cur, Frags& nxt, const Addr& at, Addr& at_next) __attribute__((always_inline)) {
         const bool last = h == KH - 1;
-        if (last) {
-            if constexpr (PROD)
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            else
-                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((NST - 2) * LOADS + LOADS0) : "memory");
-            __syncthreads();
-        }
-        const int st = (sl - s0) % NST;
-        const int rst = last ? (sl + 1 - s0) % NST : st;   // stage and k step read into nxt
-        const int rh = last ? 0 : h + 1;
-        const int rua = last ? wrap(ua + AU) : ua;
-        // the ring unit at which slice sl + NST starts: XA units before
-        // slice sl's first (NST AU = RA - XA units on)
-        const int dua = XA ? (ua >= XA ? ua - XA : ua - XA + RA) : ua;
-        const bool refill = sl + NST < s1;
-        // fragment read u goes after MFMA u * NMFMA / NPIECE (the first half
-        // of the step), DMA load q after MFMA q * NMFMA / LOADS (constant loop
+        // fragment read u goes after MFMA u * NMFMA / NPIECE in the last k
+        // step, and spread over three quarters of the first; DMA load q
+        // after MFMA 1 + q * (NMFMA - 1) / (the step's loads) (constant loop
         // bounds, so that everything unrolls and the fragments stay in
         // registers). A slice's k steps share its scales (one 128-wide k
-        // block): the last step reads the next slice's, two after each of
-        // MFMAs NMFMA / 2 .. NMFMA / 2 + 3, and makes them operands after its
-        // last MFMA; the other steps pass theirs on.
+        // block): the last step reads the next slice's, two after each MFMA
+        // from the middle on, and makes them operands a quarter step later;
+        // the first passes them on.
         if constexpr (GROUPED) {
             if (!last) {
 #pragma unroll
                 for (int fi = 0; fi < FM + FN; ++fi) nxt.sc[fi] = cur.sc[fi];
             }
         }
+        auto sc_at = [](int fi) { return SC0 + fi / 2 + SCD < NMFMA - 1 ? SC0 + fi / 2 + SCD : NMFMA - 1; };
 #pragma unroll
         for (int t = 0; t < NMFMA; ++t) {
             mfma_one(cur, t);
+            asm volatile("" : "+a"(acc[t / FN][t % FN]));
+            if (t == 0 && last) {
+                if constexpr (PROD)
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                else
+                    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((NST - 2) * LOADS + LOADS0) : "memory");
+                __syncthreads();
+            }
+            if (t == 1 && !last) {
+                pin(ua); pin(st); pin(sl);
+                un = wrap(ua + AU * UNIT);
+                stn = st + 1 == NST ? 0 : st + 1;
+                // slice sl + NST starts XA units before slice sl's first
+                // (NST AU = RA - XA units on)
+                if (!PROD)
+                    ld = slice_loads(XA ? (ua >= XA * UNIT ? ua - XA * UNIT : ua - XA * UNIT + A_RING) : ua, sl + NST,
+                                     sl + NST < s1);
+            }
+            if (t == TAT) {
+                pin(un); pin(stn);
+                at_next = address(un, stn, last ? 1 : 0);
+            }
 #pragma unroll
             for (int u = 0; u < FM + FN; ++u)
-                if (u * NMFMA / NPIECE == t) read_piece(nxt, rua, rst, rh, u);
+                if (last ? u * NMFMA / NPIECE == t : u * (NMFMA * 3 / 4) / (FM + FN) == t) read_piece(nxt, at, stn, u);
             if (last) {
 #pragma unroll
                 for (int u = FM + FN; u < NPIECE; ++u)
-                    if (NMFMA / 2 + (u - FM - FN) / 2 == t) read_piece(nxt, rua, rst, rh, u);
+                    if (SC0 + (u - FM - FN) / 2 == t) read_piece(nxt, at, stn, u);
+#pragma unroll
+                for (int fi = 0; fi < FM + FN; ++fi)
+                    if (sc_at(fi) == t) scale_e8m0(nxt, fi);
             }
             if (!PROD) {
                 constexpr int L1 = LOADS - LOADS0;
 #pragma unroll
                 for (int q = 0; q < (last ? L1 : LOADS0); ++q)
-                    if (q * NMFMA / (last ? L1 : LOADS0 ? LOADS0 : 1) == t)
-                        dma_one(dua, st, sl + NST, last ? LOADS0 + q : q, refill);
+                    if (1 + q * (NMFMA - 1) / (last ? L1 : LOADS0 ? LOADS0 : 1) == t)
+                        dma_one(ld, st, last ? LOADS0 + q : q);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (last) scales_e8m0(nxt);
     };
 
     // prologue: slices s0 .. s0 + NST - 1 in flight, then k step 0 of slice s0 read
@@ -612,7 +675,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
 #pragma unroll
         for (int t = 0; t < NST; ++t)
 #pragma unroll
-            for (int q = 0; q < LOADS; ++q) dma_one(t * AU, t, s0 + t, q, s0 + t < s1);
+            for (int q = 0; q < LOADS; ++q) dma_one(slice_loads(t * AU * UNIT, s0 + t, s0 + t < s1), t, q);
         asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NST - 1) * LOADS) : "memory");
     }
     __syncthreads();
@@ -627,7 +690,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
                 __syncthreads();
                 const int st = (sl - s0) % NST;
 #pragma unroll
-                for (int q = 0; q < LOADS; ++q) dma_one(st * AU, st, sl + NST, q, sl + NST < s1);
+                for (int q = 0; q < LOADS; ++q) dma_one(slice_loads(st * AU * UNIT, sl + NST, sl + NST < s1), st, q);
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();   // the epilogue's barrier: the ring is idle
@@ -635,25 +698,17 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
         }
     }
     Frags F0, F1;
+    Addr at0 = address(0, 0, 0), at1;
 #pragma unroll
-    for (int t = 0; t < NPIECE; ++t) read_piece(F0, 0, 0, 0, t);
-    scales_e8m0(F0);
-    int ua = 0;                                // slice sl's first unit in A's ring
-    if constexpr (KH == 2) {
-        for (int sl = s0; sl < s1; ++sl) {
-            step(sl, ua, 0, F0, F1);
-            step(sl, ua, 1, F1, F0);
-            ua = wrap(ua + AU);
-        }
-    } else {
-        int sl = s0;
-        for (; sl + 1 < s1; sl += 2) {
-            step(sl, ua, 0, F0, F1);
-            ua = wrap(ua + AU);
-            step(sl + 1, ua, 0, F1, F0);
-            ua = wrap(ua + AU);
-        }
-        if (sl < s1) step(sl, ua, 0, F0, F1);
+    for (int t = 0; t < NPIECE; ++t) read_piece(F0, at0, 0, t);
+#pragma unroll
+    for (int fi = 0; fi < FM + FN; ++fi) scale_e8m0(F0, fi);
+    at0 = address(0, 0, 1);
+    for (int sl = s0; sl < s1; ++sl) {
+        step(sl, 0, F0, F1, at0, at1);
+        step(sl, 1, F1, F0, at1, at0);
+        ua = un;
+        st = stn;
     }
     // the loads issued for slices past the end write zeros into the ring,
     // which the epilogue reuses: let them land first
@@ -936,7 +991,12 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
             // the region belongs to this wave alone
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             if constexpr (OUT == kOutSoftmaxGradQ) {
-                quantize_staged_dz(p, ep, mrow0, ncol0, lane);
+                // its arguments are read here: scalar registers that would
+                // hold them through the main loop are short
+                const __attribute__((address_space(4))) Params* kp =
+                    (const __attribute__((address_space(4))) Params*)__builtin_amdgcn_kernarg_segment_ptr();
+                asm volatile("" : "+s"(kp));
+                quantize_staged_dz(*kp, ep, mrow0, ncol0, lane);
                 return;
             }
             // iteration it: lane l takes chunk l & 15 of staged row 4 it + (l >> 4);
