@@ -122,7 +122,7 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, bool grouped, int batch = 1, boo
 // 28-layer step with the workload's operands, groups of 2 and 8 rows for
 // the short reductions over many tile columns (the gate/up Fprop, the down
 // Dgrad) measured 1% slower than 4 (results bitwise the same).
-constexpr int kGroupRows = 4;
+constexpr int kGroupRows = 4;      // (at most 4: the kernel's division by a group's rows)
 
 size_t plan_workspace_bytes(int64_t M, int64_t N, const Plan& pl, int batch = 1) {
     if (pl.splits <= 1) return 0;
@@ -165,6 +165,10 @@ void run_plan(const GemmProblem& g, const Plan& pl, void* ws, hipStream_t stream
     prm.splits = pl.splits;
     prm.tiles_m = (int)((g.M + t.bm - 1) / t.bm);
     prm.tiles_n = (int)((g.N + t.bn - 1) / t.bn);
+    const int per_split = g.upper ? prm.tiles_m * (prm.tiles_m + 1) / 2 : prm.tiles_m * prm.tiles_n;
+    prm.per_split = Divisor::of((uint32_t)per_split);
+    prm.per_problem = Divisor::of((uint32_t)per_split * (uint32_t)pl.splits);
+    prm.per_group = Divisor::of((uint32_t)(kGroupRows * prm.tiles_n));
     prm.accumulate = g.accumulate;
     prm.gm = kGroupRows;
     prm.alpha = g.alpha;
@@ -183,7 +187,7 @@ void run_plan(const GemmProblem& g, const Plan& pl, void* ws, hipStream_t stream
     prm.q8 = g.q8; prm.q8_scale = g.q8_scale; prm.q8t = g.q8t; prm.q8t_scale = g.q8t_scale;
     const bool grouped = grouped_scales(g);
     const int out = pl.splits > 1 ? 2 : g.out;
-    const int grid = (g.upper ? prm.tiles_m * (prm.tiles_m + 1) / 2 : prm.tiles_m * prm.tiles_n) * pl.splits * g.batch;
+    const int grid = per_split * pl.splits * g.batch;
     auto launch = [&](auto fa, auto fb) {
         constexpr int FA = decltype(fa)::value, FB = decltype(fb)::value;
         if (grouped) launch_variant<FA, FB, true>(prm, pl.cfg, out, grid, stream);

@@ -13,6 +13,22 @@ namespace gemm_detail {
 
 constexpr int kBK = 128;                   // k block of the grouped scales (and of split-K ranges)
 
+// Division of x < 2^31 by a positive d fixed on the host: the high word of x
+// times m = ceil(2^(32 + s) / d), shifted by s, with 2^s < d <= 2^(s + 1); m d
+// exceeds 2^(32 + s) by less than d <= 2^(s + 1), which x < 2^31 keeps from
+// reaching the quotient.
+struct Divisor {
+    uint32_t d, m, s;
+    static Divisor of(uint32_t d) {
+        Divisor r{d, 0u, 0u};
+        if (d < 2) return r;
+        while ((2u << r.s) < d) ++r.s;
+        r.m = (uint32_t)(((1ull << (32 + r.s)) + d - 1) / d);
+        return r;
+    }
+    __device__ __forceinline__ uint32_t quotient(uint32_t x) const { return d == 1 ? x : __umulhi(x, m) >> s; }
+};
+
 struct Params {
     const uint8_t* A;
     const uint8_t* B;
@@ -29,6 +45,9 @@ struct Params {
     int ksteps, ksteps_per_split, splits;
     int gm;                    // tile rows per group within an XCD's range of tiles
     int tiles_m, tiles_n;
+    Divisor per_split;         // tiles of a problem's k range,
+    Divisor per_problem;       // of a problem (per_split * splits),
+    Divisor per_group;         // and of a group of gm tile rows
     int accumulate;
     float alpha;               // host-known factor of the sums (with the per-tensor scales)
     const uint16_t* bias;      // OUT kOutBF16Epi: optional bias [N] and residual [M, N] (pitch ldr)

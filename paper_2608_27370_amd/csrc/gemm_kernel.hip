@@ -79,6 +79,11 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
+// BF16 outputs of FP8 operands are a linear layer's: far larger than the L2
+// and next read by another kernel, they are stored past the caches
+// (non-temporal). Those of BF16 operands, MuonH's, are read back at once.
+template <int FA> constexpr bool kStreamOut = FA != kBF16;
+
 constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }
 
 
@@ -305,7 +310,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     static_assert(A_BLK % NW == 0 && B_BLK % NW == 0 && LPU * NW * RPL == 64 && NW % 2 == 0, "whole loads per wave");
     static_assert(XA == 0 || (KH == 2 && !PROD && XA <= AU), "spare units");
     static_assert(NST >= 2 && (NST - 1) * LOADS + LOADS0 <= 63, "pipeline depth");
-    static_assert(WTM % 64 == 0, "a wave's rows are whole A units");
+    static_assert(XA == 0 || WTM % 64 == 0, "a wave's rows are whole A units of a wrapping ring");
 
     // A's ring, B's stages, and the grouped scales of a slice's rows (A then
     // B), float, DMA'd like the operands
@@ -324,19 +329,22 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     const int T = gridDim.x;
     const int b = blockIdx.x;
     int lt = (T % 8 == 0) ? (b % 8) * (T / 8) + b / 8 : b;
-    // a symmetric product computes only the tiles on or above the diagonal
-    const int per_split = p.upper ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
+    // (divisions by host-made multipliers, skipped where the quotient is
+    // zero: integer division is a long dependent chain, and a tile's first
+    // loads wait for this index; a symmetric product has only the tiles on or
+    // above the diagonal)
+    const int per_split = (int)p.per_split.d;
     if (p.batch > 1) {
         // problem bi of a batched launch: its operands, output and partials
-        const int bi = lt / (per_split * p.splits);
-        lt -= bi * per_split * p.splits;
+        const int bi = (int)p.per_problem.quotient((uint32_t)lt);
+        lt -= bi * (int)p.per_problem.d;
         p.A += bi * p.bsa;
         p.B += bi * p.bsb;
         p.D = reinterpret_cast<uint8_t*>(p.D) + bi * p.bsd;
         if (p.residual) p.residual += bi * p.bsr;
         p.partial += (int64_t)bi * p.splits * p.M * p.N;
     }
-    const int ks = lt / per_split;
+    const int ks = p.splits > 1 ? (int)p.per_split.quotient((uint32_t)lt) : 0;
     const int rem = lt - ks * per_split;
     int tm, tn;
     if (p.upper) {
@@ -349,21 +357,15 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
         }
         tn = tm + r;
     } else {
-        const int group = rem / (p.gm * p.tiles_n);
+        const int group = (int)p.per_group.quotient((uint32_t)rem);
         const int first_m = group * p.gm;
         const int gsz = min(p.gm, p.tiles_m - first_m);
         const int r2 = rem - group * p.gm * p.tiles_n;
-        tm = first_m + r2 % gsz;
-        tn = r2 / gsz;
+        // r2 / gsz, gsz <= 4 (2^32 / 3 rounded up: exact below 2^31)
+        tn = gsz == 4 ? r2 >> 2 : gsz == 3 ? (int)__umulhi((uint32_t)r2, 0x55555556u) : gsz == 2 ? r2 >> 1 : r2;
+        tm = first_m + r2 - tn * gsz;
     }
     const int m0 = tm * BM, n0 = tn * BN;
-    // per-tensor scales, applied to the FP32 sums in the epilogue (loaded
-    // here so that their latency hides behind the main loop)
-    float alpha = p.alpha;
-    if (OUT != 2) {
-        if (p.a_mode == kSTensor) alpha *= p.sa[0];
-        if (p.b_mode == kSTensor) alpha *= p.sb[0];
-    }
     // k slices [s0, s1): this split's 128-byte k blocks
     const int s0 = ks * p.ksteps_per_split;
     const int s1 = min((ks + 1) * p.ksteps_per_split, p.ksteps);
@@ -406,7 +408,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     // the main loop.
     uint32_t sc_base[SC_PER > 0 ? SC_PER : 1], sc_kstride[SC_PER > 0 ? SC_PER : 1];
     bool sc_is_a[SC_PER > 0 ? SC_PER : 1];
-    if constexpr (GROUPED) {
+    auto scale_setup = [&](int lane) __attribute__((always_inline)) {
         rsa = make_rsrc(p.sa, p.a_mode == kSTensor ? 0u : p.sa_bytes);
         rsb = make_rsrc(p.sb, p.b_mode == kSTensor ? 0u : p.sb_bytes);
 #pragma unroll
@@ -419,21 +421,18 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
             const int ld = is_a ? p.ld_sa : p.ld_sb;
             const int row0 = is_a ? m0 : n0;
             const int rows = is_a ? p.M : p.N;
-            int unit = -1;   // row (row scales) or 128-row block (block scales) of this lane's entry
-            if (mode == kSBlock) {
-                // the 128-row blocks the tile's rows touch: from row0's to (row0 + BM - 1)'s
-                const int b = (row0 >> 7) + r;
-                const int last = (row0 + (is_a ? BM : BN) - 1) >> 7;
-                if (b <= last && b < (rows + 127) >> 7) unit = b;
-            } else if (mode == kSRow) {
-                if (row0 + r < rows) unit = row0 + r;
-            }
+            // row (row scales) or 128-row block (block scales) of this lane's
+            // entry, and the number of them that exist or the tile touches
+            const bool blocks = mode == kSBlock;
+            const int unit = (blocks ? row0 >> 7 : row0) + r;
+            const int tile_end = ((row0 + (is_a ? BM : BN) - 1) >> 7) + 1;
+            const int end = mode == kSTensor ? 0 : blocks ? min(tile_end, (rows + 127) >> 7) : rows;
             sc_is_a[j] = is_a;
-            sc_base[j] = unit < 0 ? kOOB : (uint32_t)(km ? unit : unit * ld) * 4u;
+            sc_base[j] = unit < end ? (uint32_t)(unit * (km ? 1 : ld)) * 4u : kOOB;
             // (no stride without scales: an empty descriptor takes no offset)
             sc_kstride[j] = mode == kSTensor ? 0u : (km ? (uint32_t)ld : 1u) * 4u;
         }
-    }
+    };
     (void)sc_base; (void)sc_kstride; (void)sc_is_a;
 
     // positions in A's ring, bytes
@@ -473,12 +472,6 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     };
 
     v16f acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
     const int fr = lane & 31;                 // fragment row of this lane
     const int c0 = (lane >> 5) * 2;           // first of this lane's two chunks in a 64-byte k step
@@ -513,7 +506,8 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     // (LDS addresses: `at` holds a lane's two 16-byte chunks of the k step in
     // each of its A units' first fragment row, then in B's)
     constexpr int NPIECE = (FM + FN) * (GROUPED ? 2 : 1);
-    constexpr int UW = WTM / 64;                 // A units of a wave
+    // a wave's A units (without spare units a slice does not wrap: one run)
+    constexpr int UW = XA ? WTM / 64 : 1;
     struct Addr {
         uint32_t lo[UW + 1], hi[UW + 1];
     };
@@ -527,7 +521,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
         Addr at;
 #pragma unroll
         for (int u = 0; u <= UW; ++u) {
-            const uint32_t off = u < UW ? wrap(ua + (wm * UW + u) * UNIT) : A_RING + st * B_BYTES + wn * WTN * SL;
+            const uint32_t off = u < UW ? wrap(ua + wm * WTM * SL + u * UNIT) : A_RING + st * B_BYTES + wn * WTN * SL;
             at.lo[u] = lane_at[h][0] + off;
             at.hi[u] = lane_at[h][1] + off;
         }
@@ -535,7 +529,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     };
     auto read_piece = [&](Frags& f, const Addr& at, int st, int t) __attribute__((always_inline)) {
         if (t < FM + FN) {
-            const int u = t < FM ? t / 2 : UW, off = (t < FM ? t % 2 : t - FM) * (32 * SL);
+            const int u = t < FM ? (XA ? t / 2 : 0) : UW, off = (t < FM ? (XA ? t % 2 : t) : t - FM) * (32 * SL);
             const v4i lo = *(lds_v4i)(uintptr_t)(at.lo[u] + off);
             const v4i hi = *(lds_v4i)(uintptr_t)(at.hi[u] + off);
             f.f[t] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -602,7 +596,9 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     // the MFMAs themselves ("+a").
     constexpr int NMFMA = FM * FN;
     constexpr int SC0 = NMFMA / 2, SCD = NMFMA / 4;
-    constexpr int TAT = NMFMA > 4 ? NMFMA - 3 : 2;
+    constexpr int TAT = NMFMA > 4 ? NMFMA - 3 : NMFMA / 2, TLD = NMFMA > 1 ? 1 : 0;
+    // (a step of one MFMA takes everything after it)
+    auto load_at = [](int q, int n) { return TLD + q * (NMFMA - TLD) / (n > 0 ? n : 1); };
     int ua = 0, st = 0;                        // where slice sl starts in A's ring, its stage
     int un = 0, stn = 0;                       // the same of slice sl + 1
     Slice ld{};
@@ -610,7 +606,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
         const bool last = h == KH - 1;
         // fragment read u goes after MFMA u * NMFMA / NPIECE in the last k
         // step, and spread over three quarters of the first; DMA load q
-        // after MFMA 1 + q * (NMFMA - 1) / (the step's loads) (constant loop
+        // after MFMA load_at(q, the step's loads) (constant loop
         // bounds, so that everything unrolls and the fragments stay in
         // registers). A slice's k steps share its scales (one 128-wide k
         // block): the last step reads the next slice's, two after each MFMA
@@ -634,7 +630,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
                     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((NST - 2) * LOADS + LOADS0) : "memory");
                 __syncthreads();
             }
-            if (t == 1 && !last) {
+            if (t == TLD && !last) {
                 pin(ua); pin(st); pin(sl);
                 un = wrap(ua + AU * UNIT);
                 stn = st + 1 == NST ? 0 : st + 1;
@@ -663,21 +659,63 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
                 constexpr int L1 = LOADS - LOADS0;
 #pragma unroll
                 for (int q = 0; q < (last ? L1 : LOADS0); ++q)
-                    if (1 + q * (NMFMA - 1) / (last ? L1 : LOADS0 ? LOADS0 : 1) == t)
+                    if ((NMFMA == 1 ? 0 : load_at(q, last ? L1 : LOADS0)) == t)
                         dma_one(ld, st, last ? LOADS0 + q : q);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    // prologue: slices s0 .. s0 + NST - 1 in flight, then k step 0 of slice s0 read
+    // prologue: slices s0 .. s0 + NST - 1 in flight, then k step 0 of slice
+    // s0 read. The operands' loads issue as soon as their offsets are known,
+    // no faster than the texture unit takes them (64 bytes per clock): the
+    // scales' set-up follows slice s0's, and the accumulators are cleared
+    // between the loads (not in a deep ring's prologue, which is a loop: its
+    // addresses would not fit into the scalar registers unrolled).
+    constexpr bool kRolled = PROD || NST > 4;
+    auto clear = [&](int n, int of) __attribute__((always_inline)) {
+        constexpr int R = FM * FN;
+#pragma unroll
+        for (int e = R * n / of; e < R * (n + 1) / of; ++e) {
+            // 0 x 0 + 0: one instruction for a fragment's 16 registers
+            acc[e / FN][e % FN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v8bf{}, v8bf{}, v16f{}, 0, 0, 0);
+            asm volatile("" : "+a"(acc[e / FN][e % FN]));      // here, not earlier
+        }
+    };
     if (!PROD || producer) {
+        if constexpr (kRolled && GROUPED) scale_setup(lane);
+        auto issue = [&](int t) __attribute__((always_inline)) {
+            const Slice first = slice_loads(t * AU * UNIT, s0 + t, s0 + t < s1);
 #pragma unroll
-        for (int t = 0; t < NST; ++t)
+            for (int q = 0; q < LOADS; ++q) {
+                if constexpr (!kRolled && GROUPED) {
+                    if (t == 0 && q == A_PER + B_PER) {
+                        int l = lane;
+                        asm volatile("" : "+v"(l));
+                        scale_setup(l);
+                    }
+                }
+                dma_one(first, t, q);
+                if constexpr (!kRolled) clear(t * LOADS + q, NST * LOADS);
+            }
+        };
+        if constexpr (kRolled) {
+#pragma unroll 1
+            for (int t = 0; t < NST; ++t) issue(t);
+        } else {
 #pragma unroll
-            for (int q = 0; q < LOADS; ++q) dma_one(slice_loads(t * AU * UNIT, s0 + t, s0 + t < s1), t, q);
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NST - 1) * LOADS) : "memory");
+            for (int t = 0; t < NST; ++t) issue(t);
+        }
     }
+    if constexpr (kRolled) clear(0, 1);
+    // per-tensor scales, applied to the FP32 sums in the epilogue (loaded
+    // here so that their latency hides behind the main loop)
+    float alpha = p.alpha;
+    if (OUT != 2) {
+        if (p.a_mode == kSTensor) alpha *= p.sa[0];
+        if (p.b_mode == kSTensor) alpha *= p.sb[0];
+    }
+    if (!PROD || producer) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NST - 1) * LOADS) : "memory");
     __syncthreads();
     if constexpr (PROD) {
         if (producer) {
@@ -714,6 +752,15 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     // which the epilogue reuses: let them land first
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
+    // An accumulator read at its point of use (a copy the compiler may not
+    // hoist): otherwise it moves accumulators to VGPRs ahead of the epilogue's
+    // branches, and spills.
+    auto acc_at = [&](int i, int j, int e) __attribute__((always_inline)) {
+        float v;
+        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(acc[i][j][e]));
+        return v;
+    };
+
     // ---- The LM head's forward statistics, straight from the accumulators.
     // Of each of its rows i*32 + (l & 31), lane l holds the 64 columns
     // j*32 + 8g + 4(l >> 5) + {0..3} of the wave tile; lane l ^ 32 holds the
@@ -741,8 +788,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
             constexpr int i = decltype(i_c)::value;
             float v[FN * 16];
 #pragma unroll
-            for (int e = 0; e < FN * 16; ++e)
-                asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[e]) : "a"(acc[i][e / 16][e % 16]));
+            for (int e = 0; e < FN * 16; ++e) v[e] = acc_at(i, e / 16, e % 16);
             if (alpha != 1.0f) {
 #pragma unroll
                 for (int e = 0; e < FN * 16; ++e) v[e] *= alpha;
@@ -902,77 +948,112 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
             (void)bq;
-            // one fragment row i of the wave tile; `onehot` when some lane's
+            // Stores: chunk l & 15 of staged row 4 it + (l >> 4) in iteration
+            // it; (r & 15) repeats every 4 iterations, so four lane addresses
+            // serve all of them with compile-time offsets.
+            typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+            const int rl = lane >> 4, cl = lane & 15;
+            uint32_t la[4];
+#pragma unroll
+            for (int ph = 0; ph < 4; ++ph) {
+                const int r = 4 * ph + rl;
+                la[ph] = r * 256 + ((cl ^ (r & 15)) << 4);
+            }
+            const uint32_t row_bytes = (uint32_t)(p.ldd * 2);
+            const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
+                reinterpret_cast<uint8_t*>(p.D) + ((int64_t)mrow0 * p.ldd + ncol0) * 2, 0,
+                (int)((WTM - 1) * row_bytes + WTN * 2), 0x00020000);
+            const int voff = (int)(rl * row_bytes + cl * 16);
+            (void)la; (void)rd; (void)voff;
+            // one fragment (i, j) of the wave tile; `onehot` when some lane's
             // row has its target among the lane's columns of this wave tile
             // (a few rows in a hundred), else dz is g e throughout
-            auto stage_row = [&](auto scaled, auto onehot, auto epi, int i) __attribute__((always_inline)) {
-                {
-                    const int r = i * 32 + (lane & 31);
+            auto stage_one = [&](auto scaled, auto onehot, auto epi, int i, int j) __attribute__((always_inline)) {
+                const int r = i * 32 + (lane & 31);
 #pragma unroll
-                    for (int j = 0; j < FN; ++j) {
-#pragma unroll
-                        for (int g = 0; g < 4; ++g) {
-                            // read at the point of use (a copy the compiler
-                            // may not hoist): otherwise it moves accumulators
-                            // to VGPRs ahead of the branch, and spills
-                            float v0, v1, v2, v3;
-                            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v0) : "a"(acc[i][j][4 * g]));
-                            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v1) : "a"(acc[i][j][4 * g + 1]));
-                            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v2) : "a"(acc[i][j][4 * g + 2]));
-                            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v3) : "a"(acc[i][j][4 * g + 3]));
-                            if constexpr (decltype(scaled)::value) {
-                                v0 *= alpha; v1 *= alpha; v2 *= alpha; v3 *= alpha;
-                            }
-                            if constexpr (kDz) {
-                                // the four sums are columns j*32 + 8g + {0..3} past the
-                                // lane's first: tr is the target's position among them
-                                const int tr = row_tgt[i] - (j * 32 + 8 * g);
-                                const float P = row_p[i], K = row_k[i], gs = p.grad_scale;
-                                auto dz = [&](float z, int c) __attribute__((always_inline)) {
-                                    // 2^(z log2 e - lse log2 e) = 2^t (1 + c)
-                                    const float e = __builtin_amdgcn_exp2f(fmaf(z, kL2eHi, -P)) * fmaf(z, kL2eLoLn2, K);
-                                    if constexpr (decltype(onehot)::value) return fmaf(gs, e, c == tr ? -gs : 0.0f);
-                                    else return gs * e;
-                                };
-                                v0 = dz(v0, 0); v1 = dz(v1, 1); v2 = dz(v2, 2); v3 = dz(v3, 3);
-                            }
-                            const int u = j * 8 + 2 * g + (lane >> 5);
-                            uint2* const pos = reinterpret_cast<uint2*>(ep + r * 256 + ((u ^ (2 * (r & 15))) << 3));
-                            if constexpr (OUT == kOutBF16Epi) {
-                                // each term only when given: adding +0 would turn a -0 sum into +0
-                                if constexpr ((decltype(epi)::value & 1) != 0) {
-                                    const uint2 b = bq[j * 4 + g];
-                                    v0 += bf16lo(b.x); v1 += bf16hi(b.x); v2 += bf16lo(b.y); v3 += bf16hi(b.y);
-                                }
-                                if constexpr ((decltype(epi)::value & 2) != 0) {
-                                    const uint2 rv = *pos;
-                                    const float rs = p.res_scale;
-                                    v0 = fmaf(rs, bf16lo(rv.x), v0); v1 = fmaf(rs, bf16hi(rv.x), v1);
-                                    v2 = fmaf(rs, bf16lo(rv.y), v2); v3 = fmaf(rs, bf16hi(rv.y), v3);
-                                }
-                            }
-                            *pos = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
-                        }
-                        // one fragment at a time: otherwise every accumulator
-                        // is read into VGPRs before the first write
-                        __builtin_amdgcn_sched_barrier(0);
+                for (int g = 0; g < 4; ++g) {
+                    float v0 = acc_at(i, j, 4 * g), v1 = acc_at(i, j, 4 * g + 1);
+                    float v2 = acc_at(i, j, 4 * g + 2), v3 = acc_at(i, j, 4 * g + 3);
+                    if constexpr (decltype(scaled)::value) {
+                        v0 *= alpha; v1 *= alpha; v2 *= alpha; v3 *= alpha;
                     }
+                    if constexpr (kDz) {
+                        // the four sums are columns j*32 + 8g + {0..3} past the
+                        // lane's first: tr is the target's position among them
+                        const int tr = row_tgt[i] - (j * 32 + 8 * g);
+                        const float P = row_p[i], K = row_k[i], gs = p.grad_scale;
+                        auto dz = [&](float z, int c) __attribute__((always_inline)) {
+                            // 2^(z log2 e - lse log2 e) = 2^t (1 + c)
+                            const float e = __builtin_amdgcn_exp2f(fmaf(z, kL2eHi, -P)) * fmaf(z, kL2eLoLn2, K);
+                            if constexpr (decltype(onehot)::value) return fmaf(gs, e, c == tr ? -gs : 0.0f);
+                            else return gs * e;
+                        };
+                        v0 = dz(v0, 0); v1 = dz(v1, 1); v2 = dz(v2, 2); v3 = dz(v3, 3);
+                    }
+                    const int u = j * 8 + 2 * g + (lane >> 5);
+                    uint2* const pos = reinterpret_cast<uint2*>(ep + r * 256 + ((u ^ (2 * (r & 15))) << 3));
+                    if constexpr (OUT == kOutBF16Epi) {
+                        // each term only when given: adding +0 would turn a -0 sum into +0
+                        if constexpr ((decltype(epi)::value & 1) != 0) {
+                            const uint2 b = bq[j * 4 + g];
+                            v0 += bf16lo(b.x); v1 += bf16hi(b.x); v2 += bf16lo(b.y); v3 += bf16hi(b.y);
+                        }
+                        if constexpr ((decltype(epi)::value & 2) != 0) {
+                            const uint2 rv = *pos;
+                            const float rs = p.res_scale;
+                            v0 = fmaf(rs, bf16lo(rv.x), v0); v1 = fmaf(rs, bf16hi(rv.x), v1);
+                            v2 = fmaf(rs, bf16lo(rv.y), v2); v3 = fmaf(rs, bf16hi(rv.y), v3);
+                        }
+                    }
+                    *pos = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
+                }
+            };
+            // Fragment row i is staged while row i - 1 leaves: after each
+            // fragment, two of the eight 16-byte chunks of row i - 1 that the
+            // lane stores, whose LDS reads were issued before it. (The region
+            // belongs to this wave alone, and LDS takes a wave's accesses in
+            // their order: no wait between writing a row and reading it.)
+            constexpr bool kStore = OUT != kOutSoftmaxGradQ;
+            constexpr int AUX = OUT != kOutSoftmaxGrad && kStreamOut<FA> ? 2 : 0;   // 2: the non-temporal bit
+            auto stage_row = [&](auto scaled, auto onehot, auto epi, auto i_c) __attribute__((always_inline)) {
+                constexpr int i = decltype(i_c)::value;
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    v4u d[2];
+                    if constexpr (kStore && i > 0) {
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            const int it = (i - 1) * 8 + 2 * j + e, ph = it % 4;
+                            d[e] = *reinterpret_cast<const v4u*>(ep + la[ph] + (it - ph) * 4 * 256);
+                        }
+                    }
+                    if constexpr (i < FM) stage_one(scaled, onehot, epi, i, j);
+                    if constexpr (kStore && i > 0) {
+#pragma unroll
+                        for (int e = 0; e < 2; ++e)
+                            __builtin_amdgcn_raw_buffer_store_b128(d[e], rd, voff,
+                                                                   (int)(((i - 1) * 8 + 2 * j + e) * 4 * row_bytes), AUX);
+                    }
+                    (void)d;
+                    // one fragment at a time: otherwise every accumulator
+                    // is read into VGPRs before the first write
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             };
             auto stage = [&](auto scaled, auto epi) __attribute__((always_inline)) {
-#pragma unroll
-                for (int i = 0; i < FM; ++i) {
-                    if constexpr (kDz) {
+                static_for<FM + 1>([&](auto i_c) __attribute__((always_inline)) {
+                    constexpr int i = decltype(i_c)::value;
+                    if constexpr (kDz && i < FM) {
                         // set for the lane that holds its row's target (and
                         // maybe for its partner lane): a wave-uniform branch
                         if (__builtin_amdgcn_ballot_w64((unsigned)row_tgt[i] < (unsigned)WTN))
-                            stage_row(scaled, std::true_type{}, epi, i);
+                            stage_row(scaled, std::true_type{}, epi, i_c);
                         else
-                            stage_row(scaled, std::false_type{}, epi, i);
+                            stage_row(scaled, std::false_type{}, epi, i_c);
                     } else {
-                        stage_row(scaled, std::false_type{}, epi, i);
+                        stage_row(scaled, std::false_type{}, epi, i_c);
                     }
-                }
+                });
             };
             // epi: bit 0 a bias, bit 1 a residual (bias / residual epilogue only)
             auto stage_epi = [&](auto epi) __attribute__((always_inline)) {
@@ -988,51 +1069,16 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
             } else {
                 stage_epi(std::integral_constant<int, 0>{});
             }
-            // the region belongs to this wave alone
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             if constexpr (OUT == kOutSoftmaxGradQ) {
+                // the region belongs to this wave alone
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 // its arguments are read here: scalar registers that would
                 // hold them through the main loop are short
                 const __attribute__((address_space(4))) Params* kp =
                     (const __attribute__((address_space(4))) Params*)__builtin_amdgcn_kernarg_segment_ptr();
                 asm volatile("" : "+s"(kp));
                 quantize_staged_dz(*kp, ep, mrow0, ncol0, lane);
-                return;
             }
-            // iteration it: lane l takes chunk l & 15 of staged row 4 it + (l >> 4);
-            // (r & 15) repeats every 4 iterations, so four lane addresses serve
-            // all of them with compile-time offsets
-            typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-            const int rl = lane >> 4, cl = lane & 15;
-            uint32_t la[4];
-#pragma unroll
-            for (int ph = 0; ph < 4; ++ph) {
-                const int r = 4 * ph + rl;
-                la[ph] = r * 256 + ((cl ^ (r & 15)) << 4);
-            }
-            const uint32_t row_bytes = (uint32_t)(p.ldd * 2);
-            const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
-                reinterpret_cast<uint8_t*>(p.D) + ((int64_t)mrow0 * p.ldd + ncol0) * 2, 0,
-                (int)((WTM - 1) * row_bytes + WTN * 2), 0x00020000);
-            const int voff = (int)(rl * row_bytes + cl * 16);
-            constexpr int IT16 = WTM / 4, EG16 = 4;
-            auto store_all = [&](auto nt_c) __attribute__((always_inline)) {
-                constexpr int AUX = decltype(nt_c)::value ? 2 : 0;   // 2: the non-temporal bit
-#pragma unroll
-                for (int g0 = 0; g0 < IT16; g0 += EG16) {
-                    v4u d[EG16];
-#pragma unroll
-                    for (int e = 0; e < EG16; ++e) {
-                        const int it = g0 + e, ph = it % 4;
-                        d[e] = *reinterpret_cast<const v4u*>(ep + la[ph] + (it - ph) * 4 * 256);
-                    }
-#pragma unroll
-                    for (int e = 0; e < EG16; ++e)
-                        __builtin_amdgcn_raw_buffer_store_b128(d[e], rd, voff, (int)((g0 + e) * 4 * row_bytes), AUX);
-                }
-            };
-            if (p.nt_out) store_all(std::true_type{});
-            else store_all(std::false_type{});
             return;
         }
     }
@@ -1085,8 +1131,8 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const int chunk = j * 8 + g * 2 + (lane >> 5);
-                    float4 v = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
-                                           acc[i][j][4 * g + 3]);
+                    const float4 v = make_float4(acc_at(i, j, 4 * g), acc_at(i, j, 4 * g + 1),
+                                                 acc_at(i, j, 4 * g + 2), acc_at(i, j, 4 * g + 3));
                     *reinterpret_cast<float4*>(ep + r * ROWB + ((chunk ^ (r & SWZ)) << 4)) = v;
                 }
         }
