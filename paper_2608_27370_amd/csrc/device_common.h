@@ -41,6 +41,8 @@ __device__ __forceinline__ uint16_t to_bf16(float a) { return (uint16_t)pack_bf1
 // the low part of log2 e) applied as a first-order factor, so that the error
 // does not grow with |x|. Overflows to infinity above x = 88.72 and gives 0
 // below -103; e^(+inf) = inf, e^(-inf) = 0, NaN stays NaN.
+// NEAR: |x| < 100 is known.
+template <bool NEAR = false>
 __device__ __forceinline__ float exp_f32(float x) {
     constexpr float kL2eHi = 1.44269502162933349609375f;      // log2 e rounded to binary32
     constexpr float kL2eLo = 1.925962989e-8f;                 // log2 e - kL2eHi
@@ -48,7 +50,7 @@ __device__ __forceinline__ float exp_f32(float x) {
     const float t = x * kL2eHi;
     // the correction only where it matters and stays finite (the result is
     // exactly 0 or infinity beyond)
-    const float err = fabsf(x) < 100.0f ? fmaf(x, kL2eHi, -t) + x * kL2eLo : 0.0f;   // x log2 e - t
+    const float err = NEAR || fabsf(x) < 100.0f ? fmaf(x, kL2eHi, -t) + x * kL2eLo : 0.0f;   // x log2 e - t
     return __builtin_amdgcn_exp2f(t) * (1.0f + err * kLn2);
 }
 
@@ -74,6 +76,11 @@ __device__ __forceinline__ float exp_split(float x, int& n) {
 // evaluation, which then gives -0 as binary32 arithmetic does.
 constexpr float kDeepGate = -64.0f;
 constexpr float kFarGate = -192.0f;
+// The BF16 pattern of -kDeepGate. Where all gates of a wave lie within it in
+// magnitude (any gate a model meets), the functions below are straight-line
+// code (NEAR): a branch per element, however rarely taken, keeps the
+// exponentials and reciprocals of neighbouring elements from overlapping.
+constexpr uint32_t kNearGateBits = 0x4280u;
 
 // x * y * z * e^g for g in [kFarGate, kDeepGate): the factors' significands
 // multiplied (magnitude in [1/8, 2)) and the exponents added, then one ldexp,
@@ -93,17 +100,21 @@ __device__ __forceinline__ float mul_exp_deep(float x, float y, float z, float g
 // 1 ulp); altogether within about 5 ulp of the exact value. Deep in the
 // negative tail (g < -64) silu(g) u = g u e^g in the scaled form above, so
 // that no step flushes a value below binary32's normal range to zero.
+template <bool NEAR>
 __device__ __forceinline__ float swiglu1(float g, float u) {
-    if (g < kDeepGate && g >= kFarGate) return mul_exp_deep(g, u, 1.0f, g);
-    return g * __builtin_amdgcn_rcpf(1.0f + exp_f32(-g)) * u;
+    if constexpr (!NEAR) {
+        if (g < kDeepGate && g >= kFarGate) return mul_exp_deep(g, u, 1.0f, g);
+    }
+    return g * __builtin_amdgcn_rcpf(1.0f + exp_f32<NEAR>(-g)) * u;
 }
 
 // Eight SwiGLU values, BF16 (round to nearest even), from four words of gate
 // values and four words of up values (two BF16 values per word, low first).
+template <bool NEAR>
 __device__ __forceinline__ void swiglu8(const uint32_t g[4], const uint32_t u[4], uint32_t h[4]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        h[i] = pack_bf16x2(swiglu1(bf16lo(g[i]), bf16lo(u[i])), swiglu1(bf16hi(g[i]), bf16hi(u[i])));
+        h[i] = pack_bf16x2(swiglu1<NEAR>(bf16lo(g[i]), bf16lo(u[i])), swiglu1<NEAR>(bf16hi(g[i]), bf16hi(u[i])));
 }
 
 // The SwiGLU's backward for one element in binary32: from dH and the saved
@@ -115,6 +126,17 @@ __device__ __forceinline__ float swiglu_bwd1(float dh, float g, float u, bool dg
     if (g < kDeepGate && g >= kFarGate) return dg ? mul_exp_deep(dh, u, 1.0f + g, g) : mul_exp_deep(dh, g, 1.0f, g);
     const float sg = __builtin_amdgcn_rcpf(1.0f + exp_f32(-g));
     return dg ? dh * u * (sg * fmaf(g, 1.0f - sg, 1.0f)) : dh * (g * sg);
+}
+
+// Both of them, (dg, du), from one evaluation of s: the same values.
+template <bool NEAR>
+__device__ __forceinline__ float2 swiglu_bwd2(float dh, float g, float u) {
+    if constexpr (!NEAR) {
+        if (g < kDeepGate && g >= kFarGate)
+            return make_float2(mul_exp_deep(dh, u, 1.0f + g, g), mul_exp_deep(dh, g, 1.0f, g));
+    }
+    const float sg = __builtin_amdgcn_rcpf(1.0f + exp_f32<NEAR>(-g));
+    return make_float2(dh * u * (sg * fmaf(g, 1.0f - sg, 1.0f)), dh * (g * sg));
 }
 
 // Eight RMSNorm outputs, BF16 (round to nearest even): x * r * gamma in
@@ -274,6 +296,27 @@ __device__ __forceinline__ int pow2_exponent_bf16(uint32_t mag, bool floor_rule 
     int e = ef - 127 - Fp8Traits<FMT>::kEmax + (!floor_rule && (bits & 0x7FFFFFu) > 0x600000u ? 1 : 0);
     return e < -127 ? -127 : (e > 127 ? 127 : e);
 }
+
+// pow2_exponent_bf16 without branches, for plain groups: a finite amax whose
+// exponent stays above -127 (or zero) and, under the floor rule, whose values
+// stay within the format. Anything else takes the careful path: exponent()
+// keeps, over the groups it is given, the largest distance of amax above the
+// least plain one (as unsigned, so that smaller amax wrap to the top) and the
+// largest significand, and any() says whether one of them was not plain.
+template <int FMT>
+struct PlainExponents {
+    static constexpr uint32_t kLeast = (uint32_t)(Fp8Traits<FMT>::kEmax + 1) << 7;   // exponent -126
+    uint32_t span = 0, significand = 0;
+    __device__ __forceinline__ int exponent(uint32_t mag, bool floor_rule) {
+        const uint32_t m = mag == 0u ? (uint32_t)(127 + Fp8Traits<FMT>::kEmax) << 7 : mag;   // 2^0
+        span = max(span, m - kLeast);
+        significand = max(significand, m & 0x7Fu);
+        return (int)(m >> 7) - 127 - Fp8Traits<FMT>::kEmax + (!floor_rule && (m & 0x7Fu) > 0x60u ? 1 : 0);
+    }
+    __device__ __forceinline__ bool any(bool floor_rule) const {
+        return span > 0x7F7Fu - kLeast || (floor_rule && significand > 0x60u);
+    }
+};
 
 // Under the floor rule, whether a group with this amax (BF16 magnitude
 // pattern) can hold values beyond FMAX after scaling (significand > 1.75).

@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "device_common.h"
 #include "kernels.h"
@@ -41,6 +42,24 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, 64));
     return v;
+}
+
+// Whether no (active) lane of the wave has `c`.
+__device__ __forceinline__ bool wave_none(bool c) { return __builtin_amdgcn_ballot_w64(c) == 0; }
+
+// Maxima across lanes without LDS: over a row of 16 lanes by rotations within
+// it (every lane gets it), and of the lanes 16 or 32 apart by row swaps.
+__device__ __forceinline__ uint32_t row16_max(uint32_t v) {
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, false));   // row_ror:8
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xF, 0xF, false));   // row_ror:4
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xF, 0xF, false));   // row_ror:2
+    return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xF, 0xF, false));   // row_ror:1
+}
+__device__ __forceinline__ uint32_t pk_max_rows(uint32_t v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = pk_max_u16(a[0], a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return pk_max_u16(b[0], b[1]);
 }
 
 // Block-wide max of a per-thread value (256 threads); result in every thread.
@@ -99,15 +118,29 @@ __global__ __launch_bounds__(kThreads) void amax_partial_kernel(AmaxJob j0, Amax
                 if constexpr (SRC == kSrcSwiglu) vu[u] = *reinterpret_cast<const uint4*>(p + 8 * cpr);
             }
         }
+        auto maxima = [&](auto near_c) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-            if constexpr (SRC == kSrcSwiglu) {
-                const uint32_t wu[4] = {vu[u].x, vu[u].y, vu[u].z, vu[u].w};
-                const uint32_t wg[4] = {w[0], w[1], w[2], w[3]};
-                swiglu8(wg, wu, w);
+            for (int u = 0; u < U; ++u) {
+                uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+                if constexpr (SRC == kSrcSwiglu) {
+                    const uint32_t wu[4] = {vu[u].x, vu[u].y, vu[u].z, vu[u].w};
+                    const uint32_t wg[4] = {w[0], w[1], w[2], w[3]};
+                    swiglu8<decltype(near_c)::value>(wg, wu, w);
+                }
+                m = max(m, absmax_bits8(w));
             }
-            m = max(m, absmax_bits8(w));
+        };
+        if constexpr (SRC == kSrcSwiglu) {
+            uint32_t gm = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+                gm = max(gm, absmax_bits8(w));
+            }
+            if (wave_none(gm > kNearGateBits)) maxima(std::true_type{});
+            else maxima(std::false_type{});
+        } else {
+            maxima(std::true_type{});
         }
     }
     m = block_max(m, red);
@@ -241,6 +274,49 @@ __device__ __forceinline__ void load_swiglu_bwd_8x8(const QuantArgs& a, const Ti
     }
 }
 
+// Both halves at the thread's 8x8 block of dH's columns: the same values from
+// one read of dH, g and u (t: a tile of the F columns, F = a.cols / 2).
+__device__ __forceinline__ void load_swiglu_bwd_pair(const QuantArgs& a, const Tile& t, uint32_t dg[8][4],
+                                                     uint32_t du[8][4]) {
+    const int64_t F = a.cols / 2;
+    const int64_t tr0 = t.row0 - t.rg * 8;
+    const int64_t vr = max((int64_t)0, min((int64_t)kTile, a.rows - tr0));
+    const __amdgpu_buffer_rsrc_t rh = buffer_rsrc(a.x + tr0 * a.ld, vr == 0 ? 0u : (uint32_t)(((vr - 1) * a.ld + F) * 2));
+    const __amdgpu_buffer_rsrc_t rg =
+        buffer_rsrc(a.x2 + tr0 * a.ld2, vr == 0 ? 0u : (uint32_t)(((vr - 1) * a.ld2 + 2 * F) * 2));
+    v4i h[8], g[8], u[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int64_t r = t.rg * 8 + i;
+        const uint32_t oh = t.col_ok ? (uint32_t)((r * a.ld + t.col) * 2) : kOOB;
+        const uint32_t og = t.col_ok ? (uint32_t)((r * a.ld2 + t.col) * 2) : kOOB;
+        h[i] = __builtin_amdgcn_raw_buffer_load_b128(rh, oh, 0, 0);
+        g[i] = __builtin_amdgcn_raw_buffer_load_b128(rg, og, 0, 0);
+        u[i] = __builtin_amdgcn_raw_buffer_load_b128(rg, og, (int)(F * 2), 0);
+    }
+    // a row of eight elements at a time: their chains overlap, and more of
+    // them would not fit into the registers
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const uint32_t hw[4] = {(uint32_t)h[i].x, (uint32_t)h[i].y, (uint32_t)h[i].z, (uint32_t)h[i].w};
+        const uint32_t gw[4] = {(uint32_t)g[i].x, (uint32_t)g[i].y, (uint32_t)g[i].z, (uint32_t)g[i].w};
+        const uint32_t uw[4] = {(uint32_t)u[i].x, (uint32_t)u[i].y, (uint32_t)u[i].z, (uint32_t)u[i].w};
+        auto values = [&](auto near_c) __attribute__((always_inline)) {
+            constexpr bool NEAR = decltype(near_c)::value;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float2 lo = swiglu_bwd2<NEAR>(bf16lo(hw[j]), bf16lo(gw[j]), bf16lo(uw[j]));
+                const float2 hi = swiglu_bwd2<NEAR>(bf16hi(hw[j]), bf16hi(gw[j]), bf16hi(uw[j]));
+                dg[i][j] = pack_bf16x2(lo.x, hi.x);
+                du[i][j] = pack_bf16x2(lo.y, hi.y);
+            }
+        };
+        if (wave_none(absmax_bits8(gw) > kNearGateBits)) values(std::true_type{});
+        else values(std::false_type{});
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 template <int SRC>
 __device__ __forceinline__ void load_8x8(const QuantArgs& a, const Tile& t, uint32_t w[8][4]) {
     if constexpr (SRC == kSrcSwigluBwd) {
@@ -266,10 +342,13 @@ __device__ __forceinline__ void load_8x8(const QuantArgs& a, const Tile& t, uint
         }
     }
     if constexpr (SRC == kSrcSwiglu) {
+        // a row of eight elements at a time, as above
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const uint32_t g[4] = {w[i][0], w[i][1], w[i][2], w[i][3]};
-            swiglu8(g, wu[i], w[i]);
+            if (wave_none(absmax_bits8(g) > kNearGateBits)) swiglu8<true>(g, wu[i], w[i]);
+            else swiglu8<false>(g, wu[i], w[i]);
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
     if constexpr (SRC == kSrcRmsnorm) {
@@ -470,36 +549,49 @@ __global__ __launch_bounds__(kThreads) void quant_tensor_kernel(QuantArgs a0, Qu
     if (a.qT) store_transposed(a, t, (int64_t)(tile / gx) * kTile, (int64_t)(tile % gx) * kTile, c, tq);
 }
 
-// 1x128 row groups (q, scale) and/or 128x1 column groups (qT, scaleT).
-template <int FMT, bool ROWS, bool COLS, int SRC>
-__global__ __launch_bounds__(kThreads) void quant_groups_kernel(QuantArgs a) {
-    __shared__ uint32_t colmax[4][kTile / 2];     // packed pairs of column maxima per wave
-    __shared__ __attribute__((aligned(16))) uint8_t tq[COLS ? kTile * kTile : 16];
-    const Tile t = tile_coords(a.cols);
-    uint32_t w[8][4];
-    load_8x8<SRC>(a, t, w);
+// 1x128 row groups (q, scale) and/or 128x1 column groups (qT, scaleT) of the
+// tile in tile column bx and tile row by, from the BF16 values w of every
+// thread's 8x8 block. colmax: packed pairs of column maxima per wave; tq: the
+// transposed copy's staging.
+template <int FMT, bool ROWS, bool COLS>
+__device__ __forceinline__ void quant_groups_tile(const QuantArgs& a, const Tile& t, int64_t bx, int64_t by,
+                                                  const uint32_t w[8][4], uint32_t (*colmax)[kTile / 2], uint8_t* tq) {
     const bool floor_rule = a.pow2 == 2;
 
     if constexpr (ROWS) {
         uint2 c[8];
         float srow[8];
+        uint32_t m[8];
+        int e[8];
+        PlainExponents<FMT> plain;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            uint32_t m = absmax_bits8(w[i]);
+            m[i] = row16_max(absmax_bits8(w[i]));
+            e[i] = plain.exponent(m[i], floor_rule);
+        }
+        if (wave_none(plain.any(floor_rule))) {
+            // straight-line for all eight rows
 #pragma unroll
-            for (int o = 8; o >= 1; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 16));
-            if (m <= 0x7F7Fu) {                      // finite group
-                const int e = pow2_exponent_bf16<FMT>(m, floor_rule);
-                srow[i] = exp2i(e);
-                if (floor_rule && floor_rule_saturates(m)) c[i] = encode8<FMT, true>(w[i], exp2i(-e));
-                else if (e > -127) c[i] = encode8_pow2<FMT>(w[i], srow[i]);
-                else c[i] = encode8<FMT, false>(w[i], exp2i(-e));
-            } else if (m == 0x7F80u) {               // an infinity: largest scale, saturate
-                srow[i] = exp2i(127);
-                c[i] = encode8<FMT, true>(w[i], exp2i(-127));
-            } else {                                 // a NaN: NaN scale, NaN codes
-                srow[i] = __uint_as_float(0x7FC00000u);
-                c[i] = encode8<FMT, true>(w[i], srow[i]);
+            for (int i = 0; i < 8; ++i) {
+                srow[i] = exp2i(e[i]);
+                c[i] = encode8_pow2<FMT>(w[i], srow[i]);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (m[i] <= 0x7F7Fu) {                      // finite group
+                    const int ei = pow2_exponent_bf16<FMT>(m[i], floor_rule);
+                    srow[i] = exp2i(ei);
+                    if (floor_rule && floor_rule_saturates(m[i])) c[i] = encode8<FMT, true>(w[i], exp2i(-ei));
+                    else if (ei > -127) c[i] = encode8_pow2<FMT>(w[i], srow[i]);
+                    else c[i] = encode8<FMT, false>(w[i], exp2i(-ei));
+                } else if (m[i] == 0x7F80u) {               // an infinity: largest scale, saturate
+                    srow[i] = exp2i(127);
+                    c[i] = encode8<FMT, true>(w[i], exp2i(-127));
+                } else {                                    // a NaN: NaN scale, NaN codes
+                    srow[i] = __uint_as_float(0x7FC00000u);
+                    c[i] = encode8<FMT, true>(w[i], srow[i]);
+                }
             }
         }
         store_rows(a, t, c);
@@ -508,7 +600,7 @@ __global__ __launch_bounds__(kThreads) void quant_groups_kernel(QuantArgs a) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const int64_t r = t.row0 + i;
-                if (r < a.rows) a.scale[a.kmajor ? (int64_t)blockIdx.x * a.rows + r : r * ng + blockIdx.x] = srow[i];
+                if (r < a.rows) a.scale[a.kmajor ? bx * a.rows + r : r * ng + bx] = srow[i];
             }
         }
     }
@@ -522,9 +614,7 @@ __global__ __launch_bounds__(kThreads) void quant_groups_kernel(QuantArgs a) {
             uint32_t m = mag2(w[0][j]);
 #pragma unroll
             for (int i = 1; i < 8; ++i) m = pk_max_u16(m, mag2(w[i][j]));
-            m = pk_max_u16(m, (uint32_t)__shfl_xor((int)m, 16, 64));
-            m = pk_max_u16(m, (uint32_t)__shfl_xor((int)m, 32, 64));
-            cm[j] = m;
+            cm[j] = pk_max_rows(m);
         }
         const int wv = threadIdx.x >> 6;
         if ((threadIdx.x & 63) < 16) {
@@ -538,28 +628,15 @@ __global__ __launch_bounds__(kThreads) void quant_groups_kernel(QuantArgs a) {
             const int k = t.cc * 4 + j;
             cw[j] = pk_max_u16(pk_max_u16(colmax[0][k], colmax[1][k]), pk_max_u16(colmax[2][k], colmax[3][k]));
         }
-        float rcol[8], scol[8];
-        bool finite = true, normal = true;
+        float scol[8];
+        PlainExponents<FMT> plain;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const uint32_t m = (j & 1) ? (cw[j >> 1] >> 16) : (cw[j >> 1] & 0xFFFFu);
-            if (m <= 0x7F7Fu) {
-                const int e = pow2_exponent_bf16<FMT>(m, floor_rule);
-                scol[j] = exp2i(e);
-                rcol[j] = exp2i(-e);
-                normal = normal && e > -127;
-                if (floor_rule && floor_rule_saturates(m)) finite = false;   // take the saturating path
-            } else if (m == 0x7F80u) {
-                scol[j] = exp2i(127);
-                rcol[j] = exp2i(-127);
-                finite = false;
-            } else {
-                scol[j] = rcol[j] = __uint_as_float(0x7FC00000u);
-                finite = false;
-            }
+            scol[j] = exp2i(plain.exponent(m, floor_rule));
         }
         uint2 ct[8];
-        if (finite && normal) {
+        if (wave_none(plain.any(floor_rule))) {
             // transpose the BF16 block first: each column then shares one
             // scale, and its codes come out in the transposed copy's order
             uint32_t wt[8][4];
@@ -567,6 +644,25 @@ __global__ __launch_bounds__(kThreads) void quant_groups_kernel(QuantArgs a) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) ct[j] = encode8_pow2<FMT>(wt[j], scol[j]);
         } else {
+            float rcol[8];
+            bool finite = true;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t m = (j & 1) ? (cw[j >> 1] >> 16) : (cw[j >> 1] & 0xFFFFu);
+                if (m <= 0x7F7Fu) {
+                    const int e = pow2_exponent_bf16<FMT>(m, floor_rule);
+                    scol[j] = exp2i(e);
+                    rcol[j] = exp2i(-e);
+                    if (floor_rule && floor_rule_saturates(m)) finite = false;   // take the saturating path
+                } else if (m == 0x7F80u) {
+                    scol[j] = exp2i(127);
+                    rcol[j] = exp2i(-127);
+                    finite = false;
+                } else {
+                    scol[j] = rcol[j] = __uint_as_float(0x7FC00000u);
+                    finite = false;
+                }
+            }
             uint2 c[8];
             if (finite) {
 #pragma unroll
@@ -577,13 +673,78 @@ __global__ __launch_bounds__(kThreads) void quant_groups_kernel(QuantArgs a) {
             }
             transpose8x8(c, ct);
         }
-        store_transposed_ct(a, t, (int64_t)blockIdx.y * kTile, (int64_t)blockIdx.x * kTile, ct, tq);
+        store_transposed_ct(a, t, by * kTile, bx * kTile, ct, tq);
         if (t.rg == 0 && t.col_ok) {
             const int64_t ng = a.rows / kTile;
 #pragma unroll
             for (int j = 0; j < 8; ++j)
-                a.scaleT[a.kmajor ? (int64_t)blockIdx.y * a.cols + t.col + j : (t.col + j) * ng + blockIdx.y] = scol[j];
+                a.scaleT[a.kmajor ? by * a.cols + t.col + j : (t.col + j) * ng + by] = scol[j];
         }
+    }
+}
+
+template <int FMT, bool ROWS, bool COLS, int SRC>
+__global__ __launch_bounds__(kThreads) void quant_groups_kernel(QuantArgs a) {
+    __shared__ uint32_t colmax[4][kTile / 2];
+    __shared__ __attribute__((aligned(16))) uint8_t tq[COLS ? kTile * kTile : 16];
+    const Tile t = tile_coords(a.cols);
+    uint32_t w[8][4];
+    load_8x8<SRC>(a, t, w);
+    quant_groups_tile<FMT, ROWS, COLS>(a, t, blockIdx.x, blockIdx.y, w, colmax, tq);
+}
+
+// The SwiGLU's backward with both of its halves in one block: from one read
+// of dH, g and u the tile of dg in tile column bx and that of du in tile
+// column F / 128 + bx (F % 128 == 0, so no tile holds both halves). The call
+// is bound by memory and by its exponentials: a tile column at a time, as the
+// kernels above take [dg | du], reads dH and g twice (7 bytes an element of
+// dgu instead of 5, with two copies written) and evaluates the sigmoid twice.
+// dH [8192, 8960], E4M3: 1x128 + 128x1 groups 220 -> 177 us, per-tensor with
+// both copies 297 -> 251 us. Modes as the kernels': per-tensor, or row /
+// column groups; kPairAmax writes the pair's largest magnitude as a partial
+// maximum.
+enum : int { kPairAmax = 0, kPairTensor = 1, kPairRow = 2, kPairRowCol = 3, kPairCol = 4 };
+template <int FMT, int MODE>
+__global__ __launch_bounds__(kThreads) void swiglu_bwd_pair_kernel(QuantArgs a, uint32_t* partial) {
+    constexpr bool GROUPS = MODE >= kPairRow;
+    constexpr bool ROWS = MODE == kPairRow || MODE == kPairRowCol, COLS = MODE == kPairRowCol || MODE == kPairCol;
+    __shared__ uint32_t red[4];
+    __shared__ uint32_t colmax[2][4][kTile / 2];
+    __shared__ __attribute__((aligned(16))) uint8_t tq[COLS || MODE == kPairTensor ? kTile * kTile : 16];
+    const int64_t F = a.cols / 2, bx = blockIdx.x, by = blockIdx.y;
+    const Tile t = tile_coords(F, bx, by);
+    Tile tu = t;
+    tu.col += F;
+    PartialShare ps;
+    if constexpr (MODE == kPairTensor) ps = load_partials(a);
+    uint32_t dg[8][4], du[8][4];
+    load_swiglu_bwd_pair(a, t, dg, du);
+    if constexpr (MODE == kPairAmax) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) m = max(m, max(absmax_bits8(dg[i]), absmax_bits8(du[i])));
+        m = block_max(m, red);
+        if (threadIdx.x == 0) partial[by * gridDim.x + bx] = m;
+    } else if constexpr (GROUPS) {
+        quant_groups_tile<FMT, ROWS, COLS>(a, t, bx, by, dg, colmax[0], tq);
+        quant_groups_tile<FMT, ROWS, COLS>(a, tu, F / kTile + bx, by, du, colmax[1], tq);
+    } else {
+        const TensorScale sc = tensor_scale<FMT>(a, tensor_amax(a, ps, red));
+        if (bx == 0 && by == 0 && threadIdx.x == 0 && a.scale) a.scale[0] = sc.s;
+        auto half = [&](const Tile& th, const uint32_t w[8][4], int64_t col0) __attribute__((always_inline)) {
+            uint2 c[8];
+            if (sc.safe) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) c[i] = encode8<FMT, true>(w[i], sc.r);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) c[i] = encode8<FMT, false>(w[i], sc.r);
+            }
+            if (a.q) store_rows(a, th, c);
+            if (a.qT) store_transposed(a, th, by * kTile, col0, c, tq);
+        };
+        half(t, dg, bx * kTile);
+        half(tu, du, F + bx * kTile);
     }
 }
 
@@ -774,7 +935,38 @@ size_t swiglu_bwd_ws_bytes(int64_t rows, int64_t cols) {
     return ((size_t)P * sizeof(uint32_t) + 255) / 256 * 256 + sizeof(float);
 }
 
+namespace {
+
+template <int FMT>
+void launch_swiglu_bwd_pair(int mode, QuantArgs a, void* ws, hipStream_t stream) {
+    const dim3 grid((unsigned)(a.cols / 2 / kTile), (unsigned)tiles_y(a.rows));
+    uint32_t* partial = reinterpret_cast<uint32_t*>(ws);
+    switch (mode) {
+    case kQTensor:
+        swiglu_bwd_pair_kernel<FMT, kPairAmax><<<grid, kThreads, 0, stream>>>(a, partial);
+        amax_source(a, (int)(grid.x * grid.y), ws, stream);
+        swiglu_bwd_pair_kernel<FMT, kPairTensor><<<grid, kThreads, 0, stream>>>(a, partial);
+        break;
+    case kQRow:
+        if (a.qT) swiglu_bwd_pair_kernel<FMT, kPairRowCol><<<grid, kThreads, 0, stream>>>(a, partial);
+        else swiglu_bwd_pair_kernel<FMT, kPairRow><<<grid, kThreads, 0, stream>>>(a, partial);
+        break;
+    case kQCol:
+        swiglu_bwd_pair_kernel<FMT, kPairCol><<<grid, kThreads, 0, stream>>>(a, partial);
+        break;
+    }
+}
+
+}  // namespace
+
 void launch_swiglu_bwd_quantize(int fmt, int mode, QuantArgs a, void* ws, hipStream_t stream) {
+    // whole tiles in each half: both halves from one read (an odd number of
+    // 64-column half tiles, or an empty tensor, takes a tile column at a time)
+    if (a.rows > 0 && a.cols > 0 && (a.cols / 2) % kTile == 0) {
+        if (fmt == kE4M3) launch_swiglu_bwd_pair<kE4M3>(mode, a, ws, stream);
+        else launch_swiglu_bwd_pair<kE5M2>(mode, a, ws, stream);
+        return;
+    }
     if (mode == kQTensor) {
         const int64_t gx = tiles_x(a.cols), P = gx * tiles_y(a.rows);
         if (a.rows > 0 && a.cols > 0) {

@@ -108,6 +108,31 @@ def _groups_case(shape, seed, kind, specials):
 
 @pytest.mark.parametrize("rnd", [1, 2], ids=["pow2", "pow2_floor"])
 @pytest.mark.parametrize("fmt", [E4, E5])
+def test_group_exponent_edges(P, fmt, rnd):
+    """Group maxima at the ends of the scale exponents' range: subnormal, at
+    and around the least exponent that is not clamped to -127 and that of
+    scale 2^-126, with significands on both sides of 1.75, and the largest
+    finite value; one such group per row and per column."""
+    emax = 8 if fmt == E4 else 15
+    tops = [0x0001, 0x007F, 0x0080] + [((emax + d) << 7) | f for d in (-1, 0, 1, 2) for f in (0, 0x60, 0x61, 0x7F)]
+    tops += [0x7F7F, 0x7F60, 0x7F61, 0x0000]
+    x = np.zeros((128, 128), np.uint16)
+    for k, m in enumerate(tops):
+        i = 5 * k
+        x[i, i] = m
+        x[i, (i + 1) % 128] = 0x8000 | (m >> 1)
+        x[(i + 1) % 128, i] = max(m - 1, 0)
+    q, s = quant.quantize_rows_1x128(x, OFMT[fmt], RULE[rnd])
+    qT, sT = quant.quantize_cols_128x1(x, OFMT[fmt], RULE[rnd])
+    r = P.quantize_fp8(to_dev_bf16(x), fmt, P.SCALE_ROW_1x128, rnd, want_q=True, want_qT=True)
+    assert_bytes_equal(host(r["q"]), q, "row q")
+    assert_f32_bits_equal(host(r["scale"]), s, "row scale")
+    assert_bytes_equal(host(r["qT"]), qT, "col qT")
+    assert_f32_bits_equal(host(r["scaleT"]), sT, "col scaleT")
+
+
+@pytest.mark.parametrize("rnd", [1, 2], ids=["pow2", "pow2_floor"])
+@pytest.mark.parametrize("fmt", [E4, E5])
 @pytest.mark.parametrize("shape,kind,specials", [((256, 384), "normal", False), ((128, 128), "student_t", False),
                                                  ((384, 1024), "outliers", False), ((256, 384), "normal", True)])
 def test_quantize_rows_and_columns(P, fmt, shape, kind, specials, rnd):

@@ -92,6 +92,24 @@ def test_every_gate_value(P, u):
     _check_all(r, dh, gu, E4, ROW, 1, "every gate value, u = %g" % u)
 
 
+@pytest.mark.parametrize("rows,cols", [(16, 128), (144, 256), (256, 128)])
+@pytest.mark.parametrize("fmt,rnd", [(E4, 1), (E5, 0), (E5, 2)])
+def test_both_halves_in_one_block(P, rows, cols, fmt, rnd):
+    """Halves of whole 128-column tiles, whose dg and du tiles one block
+    quantises: every mode, with a ragged last row of tiles (per-tensor) and
+    rows whose gates lie in the deep tail, beyond it and just inside it."""
+    dh, gu = _inputs(130 + rows + cols, rows, cols, 8)
+    for r, g in ((3, -64.5), (4, -100.0), (9, -200.0), (11, -64.0), (12, 64.5)):
+        gu[r, 5:cols:37] = inputs.bf16_from_f64(np.array([g]))[0]
+    for want_qT in (False, True):
+        r = _run(P, dh, gu, fmt, TENSOR, rnd, want_q=True, want_qT=want_qT)
+        _check_all(r, dh, gu, fmt, TENSOR, rnd, "tensor %dx%d" % (rows, cols))
+    if rnd and rows % 128 == 0:
+        for mode, want_qT in ((ROW, False), (ROW, True), (COL, True)):
+            r = _run(P, dh, gu, fmt, mode, rnd, want_q=True, want_qT=want_qT)
+            _check_all(r, dh, gu, fmt, mode, rnd, "mode %d %dx%d" % (mode, rows, cols))
+
+
 def test_empty(P):
     dh = np.zeros((0, 64), np.uint16)
     gu = np.zeros((0, 128), np.uint16)
