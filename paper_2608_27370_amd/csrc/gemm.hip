@@ -81,11 +81,19 @@ int per_cu(const TileCfg& t, bool grouped) {
     return n < 1 ? 1 : n;
 }
 
+// Whether a problem may take the 64x64 tiles: few rows or columns, and at
+// least 24 tiles. Above 512 rows the 128x128 tiles fill enough of the chip
+// (700x2048x2048: 9.8 against 12.6 us); below 24 tiles splitting k over the
+// 128x128 ones keeps more CUs busy. Measured for single problems only.
+bool small_tiles(int64_t M, int64_t N, int64_t tiles, int batch, bool upper) {
+    return (M <= 512 || N <= 512) && tiles >= 24 && batch == 1 && !upper;
+}
+
 // Pick the tile configuration and k split with the smallest modelled time:
 // waves of work units over the CUs, each a fixed cost plus a cost per k
-// slice (lower when part of the GPU idles and the clock rises; higher with
-// block scales), plus the split-K partial sums written and read back.
-Plan make_plan(int64_t M, int64_t N, int64_t K, bool grouped, int batch = 1, bool upper = false) {
+// slice (lower when part of the GPU idles and the clock rises), plus, for a
+// split, the reduction's launch and the partial sums written and read back.
+Plan search_plan(int64_t M, int64_t N, int64_t K, bool grouped, int batch, bool upper) {
     const int ksteps = (int)((K + kBK - 1) / kBK);
     Plan best{0, 1, ksteps};
     double best_cost = -1.0;
@@ -95,6 +103,7 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, bool grouped, int batch = 1, boo
         const int64_t tm_ = (M + t.bm - 1) / t.bm, tn_ = (N + t.bn - 1) / t.bn;
         const int64_t tiles = (upper ? tm_ * (tm_ + 1) / 2 : tm_ * tn_) * batch;
         if (tiles == 0) return best;
+        if (t.bm < 128 && !small_tiles(M, N, tiles, batch, upper)) continue;
         const int64_t slots = (int64_t)kCUs * per_cu(t, grouped);
         const int max_s = (N % 4 == 0) ? (ksteps / 4 < 16 ? ksteps / 4 : 16) : 1;
         for (int s = 1; s <= (max_s > 1 ? max_s : 1); ++s) {
@@ -104,9 +113,8 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, bool grouped, int batch = 1, boo
             const int64_t units = tiles * splits;
             const int64_t waves = (units + slots - 1) / slots;
             const double busy = units < slots ? (double)units / slots : 1.0;
-            double cost = (double)waves * (t.fixed_us + t.slice_us * (kps > 0 ? kps : 1) * (1.0 - 0.332 * (1.0 - busy)));
-            if (grouped) cost *= 1.14;
-            if (splits > 1) cost += 0.289e-6 * splits * (double)M * N * 4.0 * batch;
+            double cost = (double)waves * (t.fixed_us + t.slice_us * (kps > 0 ? kps : 1) * (1.0 - 0.4 * (1.0 - busy)));
+            if (splits > 1) cost += 2.077 + 0.2342e-6 * splits * (double)M * N * 4.0 * batch;
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
                 best = Plan{c, splits, kps};
@@ -114,6 +122,27 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, bool grouped, int batch = 1, boo
         }
     }
     return best;
+}
+
+// search_plan, remembered: a call asks for its plan up to five times (its
+// workspace's size, its check, its launch), and the search's few hundred
+// divisions took longer than launching the kernel. A pure function of its
+// arguments, kept per thread in a fixed table (no locks, nothing to free).
+Plan make_plan(int64_t M, int64_t N, int64_t K, bool grouped, int batch = 1, bool upper = false) {
+    struct Entry {
+        int64_t M, N, K;
+        int batch, flags;       // flags 0: empty
+        Plan plan;
+    };
+    constexpr int kEntries = 256;
+    static thread_local Entry table[kEntries];
+    const int flags = 4 | (grouped ? 1 : 0) | (upper ? 2 : 0);
+    const uint64_t h = ((uint64_t)M * 0x9E3779B97F4A7C15ull) ^ ((uint64_t)N * 0xC2B2AE3D27D4EB4Full) ^
+                       ((uint64_t)K * 0x165667B19E3779F9ull) ^ ((uint64_t)batch << 8) ^ (uint64_t)flags;
+    Entry& e = table[(h ^ (h >> 29)) % kEntries];
+    if (e.flags != flags || e.M != M || e.N != N || e.K != K || e.batch != batch)
+        e = Entry{M, N, K, batch, flags, search_plan(M, N, K, grouped, batch, upper)};
+    return e.plan;
 }
 
 // Tile rows per group of an XCD's contiguous range of tiles (the order in

@@ -92,13 +92,21 @@ struct TileCfg {
 // often wait for queue space: the deep-ring variant adds four producer waves
 // that issue them (the tile's registers leave room for two waves per SIMD),
 // 15-20% faster on long-K Wgrad than issuing them from the MFMA waves. The
-// time constants are least-squares fits to measured kernel times on the
-// Qwen2-1.5B layer shapes.
-#define PURO_TILE_LIST(X)                                 \
-    X(0, 256, 256, 2, 2, 128, 2, 4, 0, 7.86f, 1.322f)     \
-    X(1, 256, 192, 2, 2, 128, 2, 4, 0, 6.37f, 1.120f)     \
-    X(2, 128, 128, 2, 2, 128, 4, 0, 1, 6.65f, 0.379f)     \
-    X(3, 128, 128, 2, 2, 128, 2, 0, 0, 4.37f, 0.803f)
+// 64x64 tiles are for problems of few rows, which leave most of the chip idle
+// and are bound by latency: four times the work units of 128x128, and an
+// 8-deep ring that has most of a K 1536 reduction in flight at once
+// (77x2048x1536 8.8 -> 6.0 us, 256x1536x1536 7.5 -> 6.1 us, both unsplit;
+// split over k the 128x128 tiles took 8.6 and 12.4 us with their reduction).
+// The time constants are fits to measured kernel times (graph replays, every
+// configuration and split) of 44 shapes, per-tensor and block-scaled, from 16
+// to 16384 rows: the choice is within 0.1% of the best of them on average, 4%
+// at most.
+#define PURO_TILE_LIST(X)                                  \
+    X(0, 256, 256, 2, 2, 128, 2, 4, 0, 9.150f, 1.319f)     \
+    X(1, 256, 192, 2, 2, 128, 2, 4, 0, 9.453f, 0.995f)     \
+    X(2, 128, 128, 2, 2, 128, 4, 0, 1, 6.650f, 0.3835f)    \
+    X(3, 128, 128, 2, 2, 128, 2, 0, 0, 4.063f, 0.9228f)    \
+    X(4, 64, 64, 2, 2, 128, 8, 0, 0, 2.956f, 0.3007f)
 #define PURO_TILE_ROW(i, bm, bn, wm, wn, sl, nst, xa, prod, f, s) {bm, bn, wm, wn, sl, nst, xa, prod, f, s},
 
 constexpr int kLdsBytes = 160 * 1024;

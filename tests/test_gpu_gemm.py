@@ -318,6 +318,39 @@ def test_gemm_epilogue(P, shape, terms):
                slack=mfma_model.truncation_loss_full(*op))
 
 
+# The 64x64 tiles (few rows or few columns): rows and columns that end inside
+# a tile, k tails, fewer slices than the 8-deep ring holds, exactly as many and
+# more, and a split.
+SMALL_CASES = [(16, 1536, 144), (65, 1600, 128), (77, 2060, 1552), (512, 200, 1024), (64, 2048, 4096)]
+
+
+@pytest.mark.parametrize("shape", SMALL_CASES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("scales", ["tensor", "row-block", "row-row"])
+def test_gemm_small_tiles(P, shape, scales):
+    M, N, K = shape
+    if scales == "tensor":
+        am, bm = "tensor", "tensor"
+        a, sa = _operand_tensor(61, M, K, E5, std=1e-3)
+        b, sb = _operand_tensor(62, N, K, E4, std=0.02)
+    else:
+        am, bm = scales.split("-")
+        K = -(-K // 128) * 128
+        a, sa = _operand_grouped(61, M, K, E5, am, std=1e-3)
+        b, sb = _operand_grouped(62, N, K, E4, bm, std=0.02)
+    plan = P.fp8_gemm_plan(M, N, K, MODE[am], MODE[bm])
+    assert (plan["tile_m"], plan["tile_n"]) == (64, 64), plan
+    op = (a, fp8.E5M2, sa, am, b, fp8.E4M3, sb, bm)
+    ref, den = gemm.gemm(*op)
+    for out in (0, 1):
+        D = _run(P, a, E5, sa, am, b, E4, sb, bm, out)
+        _check(P, out, D, ref, den, "small tiles %s %s out %d" % (scales, (M, N, K), out), op)
+    bias, resid = _epilogue_terms(63, M, N, True, True)
+    D = _run_epi(P, a, E5, sa, am, b, E4, sb, bm, bias, resid)
+    ref, den = gemm.epilogue(ref, den, bf16.to_f32(bias)[None, :], bf16.to_f32(resid))
+    check_bf16(bf16_bits(D), ref, den, what="small tiles epilogue %s %s" % (scales, (M, N, K)),
+               slack=mfma_model.truncation_loss_full(*op))
+
+
 # The epilogue on the tile configurations the shapes above do not reach:
 # 256x256 (the one-pass BF16 staging, whose residual block arrives in LDS by
 # DMA before the tile's stores: here in place on D), 256x192 (bias repeating
