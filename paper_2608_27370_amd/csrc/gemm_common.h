@@ -97,16 +97,20 @@ struct TileCfg {
 // 8-deep ring that has most of a K 1536 reduction in flight at once
 // (77x2048x1536 8.8 -> 6.0 us, 256x1536x1536 7.5 -> 6.1 us, both unsplit;
 // split over k the 128x128 tiles took 8.6 and 12.4 us with their reduction).
+// 256x128 fits the grids that the larger tiles leave half empty: 3968x2048x8192
+// is 256 of its tiles, one per CU (64.6 -> 57.1 us block-scaled, the LM head's
+// dX at that size; 128 tiles of 256x256 take 75 us).
 // The time constants are fits to measured kernel times (graph replays, every
 // configuration and split) of 44 shapes, per-tensor and block-scaled, from 16
-// to 16384 rows: the choice is within 0.1% of the best of them on average, 4%
-// at most.
+// to 16384 rows: the choice is within 0.3% of the best of them on average, 12%
+// at most (2304x2048x1024 at 10.9 us).
 #define PURO_TILE_LIST(X)                                  \
-    X(0, 256, 256, 2, 2, 128, 2, 4, 0, 9.150f, 1.319f)     \
-    X(1, 256, 192, 2, 2, 128, 2, 4, 0, 9.453f, 0.995f)     \
-    X(2, 128, 128, 2, 2, 128, 4, 0, 1, 6.650f, 0.3835f)    \
-    X(3, 128, 128, 2, 2, 128, 2, 0, 0, 4.063f, 0.9228f)    \
-    X(4, 64, 64, 2, 2, 128, 8, 0, 0, 2.956f, 0.3007f)
+    X(0, 256, 256, 2, 2, 128, 2, 4, 0, 9.276f, 1.343f)     \
+    X(1, 256, 192, 2, 2, 128, 2, 4, 0, 9.429f, 0.990f)     \
+    X(2, 128, 128, 2, 2, 128, 4, 0, 1, 6.424f, 0.3645f)    \
+    X(3, 128, 128, 2, 2, 128, 2, 0, 0, 4.071f, 0.8992f)    \
+    X(4, 64, 64, 2, 2, 128, 8, 0, 0, 3.031f, 0.2984f)      \
+    X(5, 256, 128, 2, 2, 128, 2, 3, 0, 6.577f, 0.7372f)
 #define PURO_TILE_ROW(i, bm, bn, wm, wn, sl, nst, xa, prod, f, s) {bm, bn, wm, wn, sl, nst, xa, prod, f, s},
 
 constexpr int kLdsBytes = 160 * 1024;

@@ -1082,6 +1082,18 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
             return;
         }
     }
+    // A tile that ends inside the matrix's last rows or columns (edge) stores
+    // the same way where its lanes' 4-column vectors lie wholly in or out
+    // (N % 4 == 0): its buffers end with its last valid row, lanes whose
+    // columns lie outside get an offset out of range, and the row offsets go
+    // into the lane offsets (as scalar operands they could exceed a buffer's
+    // size, which the range check must not see).
+    const int vrows = min(WTM, p.M - mrow0), vcols = min(WTN, p.N - ncol0);
+    if (vrows <= 0 || vcols <= 0) return;
+    const bool edge = !fast && p.N % 4 == 0 && (OUT == 2 || OUT == kOutF32 || !p.accumulate) &&
+                      (int64_t)WTM * ldo * ES <= INT32_MAX &&
+                      (OUT != kOutBF16Epi || (int64_t)WTM * p.ldr * 2 <= INT32_MAX);
+    const bool sized = fast || edge;
     // Fast-path addressing. Iteration it of a pass covers staged row r and
     // chunk c with it * 64 + lane = r * ECPR + c. That map repeats every FP
     // iterations, FR rows further on, and the rows' chunk swizzle every NPH
@@ -1100,8 +1112,8 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     for (int vv = 0; vv < FP; ++vv) {
         const int q = vv * 64 + lane;
         const int rv = q / ECPR, cv = q % ECPR;
-        goff[vv] = rv * row_bytes + cv * 4 * ES;
-        roff[vv] = rv * rrow_bytes + cv * 8;
+        goff[vv] = cv * 4 < vcols ? rv * row_bytes + cv * 4 * ES : kOOB;
+        roff[vv] = cv * 4 < vcols ? rv * rrow_bytes + cv * 8 : kOOB;
 #pragma unroll
         for (int ph = 0; ph < NPH; ++ph) {
             const int r = ph * FR + rv;
@@ -1109,14 +1121,14 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
         }
     }
     // the wave tile's output (and residual) rows as buffers: base at its
-    // first element, range over its last row's WTN elements
+    // first element, range to its last valid row's last valid element
     const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
         OUT == 2 ? (void*)(part + (int64_t)mrow0 * p.N + ncol0)
                  : (void*)(reinterpret_cast<uint8_t*>(p.D) + ((int64_t)mrow0 * p.ldd + ncol0) * ES),
-        0, fast ? (int)((WTM - 1) * row_bytes + WTN * ES) : 0, 0x00020000);
+        0, sized ? (int)((vrows - 1) * row_bytes + vcols * ES) : 0, 0x00020000);
     const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(
         OUT == kOutBF16Epi && p.residual ? const_cast<uint16_t*>(p.residual + (int64_t)mrow0 * p.ldr + ncol0) : nullptr,
-        0, OUT == kOutBF16Epi && p.residual && fast ? (int)((WTM - 1) * rrow_bytes + WTN * 2) : 0, 0x00020000);
+        0, OUT == kOutBF16Epi && p.residual && sized ? (int)((vrows - 1) * rrow_bytes + vcols * 2) : 0, 0x00020000);
     (void)laddr; (void)goff; (void)roff; (void)rd; (void)rres;
     // one pass per constant: the accumulators are indexed by the pass, and a
     // loop the unroller leaves rolled would move them to scratch memory
@@ -1141,7 +1153,7 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
         // writes only after this pass's reads have returned their data)
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         constexpr int IT = RPP * ECPR / 64;
-        if (fast) {
+        if (sized) {
             // the residual is loaded before the LDS reads of its group of
             // iterations, so that its latency overlaps those reads and the
             // group's stores wait once (a load issued after stores waits for
@@ -1152,8 +1164,16 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
             // With ACC (binary32 output added to what D holds) each group
             // first loads the outputs it replaces, with the stores' own
             // addressing, in the same place as the residual.
-            auto run_groups = [&](auto acc_c) __attribute__((always_inline)) {
+            auto run_groups = [&](auto acc_c, auto edge_c) __attribute__((always_inline)) {
                 constexpr bool ACC = decltype(acc_c)::value;
+                // where an iteration's row offset goes: the scalar operand,
+                // or (edge) the lane offset
+                auto lane_off = [](uint32_t off, uint32_t row) __attribute__((always_inline)) {
+                    return (int)(decltype(edge_c)::value ? off + row : off);
+                };
+                auto row_off = [](uint32_t row) __attribute__((always_inline)) {
+                    return (int)(decltype(edge_c)::value ? 0u : row);
+                };
                 constexpr int EG = ((OUT == kOutBF16Epi || ACC) && IT > 16) ? IT / 2 : IT;
                 static_assert(IT % EG == 0 && EG % FP == 0, "epilogue groups");
                 typedef unsigned int v4a __attribute__((ext_vector_type(4)));
@@ -1164,8 +1184,9 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
 #pragma unroll
                         for (int e = 0; e < EG; ++e) {
                             const int u = (g0 + e) / FP, vv = (g0 + e) % FP;
+                            const uint32_t row = (pass * RPP + u * FR) * row_bytes;
                             ea[e] = __builtin_bit_cast(v4a, __builtin_amdgcn_raw_buffer_load_b128(
-                                rd, (int)goff[vv], (int)((pass * RPP + u * FR) * row_bytes), 0));
+                                rd, lane_off(goff[vv], row), row_off(row), 0));
                         }
                     }
                     (void)ea;
@@ -1174,8 +1195,9 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
 #pragma unroll
                         for (int e = 0; e < EG; ++e) {
                             const int u = (g0 + e) / FP, vv = (g0 + e) % FP;
+                            const uint32_t row = (pass * RPP + u * FR) * rrow_bytes;
                             er[e] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(
-                                rres, (int)roff[vv], (int)((pass * RPP + u * FR) * rrow_bytes), 0));
+                                rres, lane_off(roff[vv], row), row_off(row), 0));
                         }
                     }
                     float4 v[EG];
@@ -1198,7 +1220,8 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
 #pragma unroll
                         for (int e = 0; e < EG; ++e) {
                             const int u = (g0 + e) / FP, vv = (g0 + e) % FP;
-                            const int soff = (int)((pass * RPP + u * FR) * row_bytes);
+                            const uint32_t row = (pass * RPP + u * FR) * row_bytes;
+                            const int voff = lane_off(goff[vv], row), soff = row_off(row);
                             float4 w = v[e];
                             if constexpr (OUT == kOutBF16Epi) {
                                 // each term only when given: adding +0 would turn a -0 sum into +0
@@ -1219,11 +1242,11 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
                                     w.x += o.x; w.y += o.y; w.z += o.z; w.w += o.w;
                                 }
                                 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-                                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, w), rd, (int)goff[vv], soff, AUX);
+                                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, w), rd, voff, soff, AUX);
                             } else {
                                 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
                                 __builtin_amdgcn_raw_buffer_store_b64(v2u{pack_bf16x2(w.x, w.y), pack_bf16x2(w.z, w.w)}, rd,
-                                                                      (int)goff[vv], soff, AUX);
+                                                                      voff, soff, AUX);
                             }
                         }
                     };
@@ -1231,12 +1254,16 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
                     else store_group(std::false_type{});
                 }
             };
-            if constexpr (OUT == kOutF32) {
-                if (p.accumulate) run_groups(std::true_type{});
-                else run_groups(std::false_type{});
-            } else {
-                run_groups(std::false_type{});
-            }
+            auto run = [&](auto edge_c) __attribute__((always_inline)) {
+                if constexpr (OUT == kOutF32) {
+                    if (p.accumulate) run_groups(std::true_type{}, edge_c);
+                    else run_groups(std::false_type{}, edge_c);
+                } else {
+                    run_groups(std::false_type{}, edge_c);
+                }
+            };
+            if (fast) run(std::false_type{});
+            else run(std::true_type{});
             return;
         }
 #pragma unroll

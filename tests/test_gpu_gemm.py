@@ -351,6 +351,37 @@ def test_gemm_small_tiles(P, shape, scales):
                slack=mfma_model.truncation_loss_full(*op))
 
 
+@pytest.mark.parametrize("shape,scales", [((3001, 2056, 2064), "tensor"), ((3968, 2048, 3072), "row-block"),
+                                          ((3900, 2040, 2560), "row-row")],
+                         ids=lambda s: s if isinstance(s, str) else "x".join(map(str, s)))
+def test_gemm_256x128_tiles(P, shape, scales):
+    """The 256x128 tiles, whose ring has three spare units: ragged rows,
+    columns and k tail (per-tensor) and block scales, every output kind, on
+    64 entries of every 256x256 block."""
+    from gpu_util import sample_entries
+    M, N, K = shape
+    am, bm = ("tensor", "tensor") if scales == "tensor" else scales.split("-")
+    if scales == "tensor":
+        a, sa = _operand_tensor(71, M, K, E4)
+        b, sb = _operand_tensor(72, N, K, E4, std=0.02)
+    else:
+        a, sa = _operand_grouped(71, M, K, E4, am)
+        b, sb = _operand_grouped(72, N, K, E4, bm, std=0.02)
+    plan = P.fp8_gemm_plan(M, N, K, MODE[am], MODE[bm])
+    assert (plan["tile_m"], plan["tile_n"], plan["splits"]) == (256, 128, 1), plan
+    op = (a, fp8.E4M3, sa, am, b, fp8.E4M3, sb, bm)
+    ms, ns = sample_entries(M, N, np.random.default_rng(73), per_tile=64, full_tiles=False)
+    ref, den = gemm.gemm_entries(ms, ns, *op)
+    slack = mfma_model.truncation_loss(ms, ns, *op)
+    what = "256x128 %s %s" % (scales, shape)
+    check_bf16(bf16_bits(_run(P, a, E4, sa, am, b, E4, sb, bm, 0))[ms, ns], ref, den, what=what, slack=slack)
+    check_fp32(host(_run(P, a, E4, sa, am, b, E4, sb, bm, 1))[ms, ns], ref, den, what=what, slack=slack)
+    bias, resid = _epilogue_terms(74, M, N, True, True)
+    D = _run_epi(P, a, E4, sa, am, b, E4, sb, bm, bias, resid)
+    ref, den = gemm.epilogue(ref, den, bf16.to_f32(bias)[ns], bf16.to_f32(resid)[ms, ns])
+    check_bf16(bf16_bits(D)[ms, ns], ref, den, what=what + " epilogue", slack=slack)
+
+
 # The epilogue on the tile configurations the shapes above do not reach:
 # 256x256 (the one-pass BF16 staging, whose residual block arrives in LDS by
 # DMA before the tile's stores: here in place on D), 256x192 (bias repeating
