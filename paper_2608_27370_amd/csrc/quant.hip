@@ -510,6 +510,22 @@ __global__ __launch_bounds__(kThreads) void tile_amax_kernel(QuantArgs a, int gx
     if (threadIdx.x == 0) partial[blockIdx.x] = m;
 }
 
+// The codes of a per-tensor quantisation's tile at (row0, col0), q and qT.
+template <int FMT>
+__device__ __forceinline__ void store_tensor_codes(const QuantArgs& a, const Tile& t, const TensorScale& sc, int64_t row0,
+                                                   int64_t col0, const uint32_t w[8][4], uint8_t* tq) {
+    uint2 c[8];
+    if (sc.safe) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) c[i] = encode8<FMT, true>(w[i], sc.r);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) c[i] = encode8<FMT, false>(w[i], sc.r);
+    }
+    if (a.q) store_rows(a, t, c);
+    if (a.qT) store_transposed(a, t, row0, col0, c, tq);
+}
+
 // Per-tensor quantisation of one or two tensors in one launch (1-D grid:
 // the first tensor's tiles, then the second's). Each block loads the partial
 // maxima of both tensors and its tile's BF16 values before reducing any of
@@ -536,17 +552,44 @@ __global__ __launch_bounds__(kThreads) void quant_tensor_kernel(QuantArgs a0, Qu
         if (a0.scale) a0.scale[0] = sc0.s;
         if (two && a1.scale) a1.scale[0] = sc1.s;
     }
-    const TensorScale sc = second ? sc1 : sc0;
-    uint2 c[8];
-    if (sc.safe) {
+    store_tensor_codes<FMT>(a, t, second ? sc1 : sc0, (int64_t)(tile / gx) * kTile, (int64_t)(tile % gx) * kTile, w, tq);
+}
+
+// Per-tensor quantisation of a small dense tensor in one launch: every block
+// reduces the whole tensor itself. A launch of its own for the maxima costs
+// 2.5 to 3 us however small the tensor; reading up to kSmallTensor elements
+// again in every block costs less (16 loads in flight per thread, from the L2
+// after the first block). Graph replays, two launches against one:
+// [16, 1536] 7.3 -> 4.2 us, [77, 1536] 6.6 -> 5.2, [64, 2048] with both copies
+// 6.9 -> 5.7; twice that size would be even.
+constexpr int64_t kSmallTensor = 131072;
+template <int FMT>
+__global__ __launch_bounds__(kThreads) void quant_tensor_small_kernel(QuantArgs a, int gx) {
+    __shared__ uint32_t red[4];
+    __shared__ __attribute__((aligned(16))) uint8_t tq[kTile * kTile];
+    const int tile = (int)blockIdx.x;
+    const Tile t = tile_coords(a.cols, tile % gx, tile / gx);
+    const uint32_t bytes = (uint32_t)(a.rows * a.cols * 2);
+    const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(a.x, bytes);
+    constexpr int U = 16;
+    uint32_t m = 0;
+    for (uint32_t o = threadIdx.x * 16; o < bytes; o += kThreads * 16 * U) {
+        v4i v[U];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) c[i] = encode8<FMT, true>(w[i], sc.r);
-    } else {
+        for (int u = 0; u < U; ++u)     // past the end: zeros
+            v[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, o + u * kThreads * 16, 0, 0);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) c[i] = encode8<FMT, false>(w[i], sc.r);
+        for (int u = 0; u < U; ++u) {
+            const uint32_t w[4] = {(uint32_t)v[u].x, (uint32_t)v[u].y, (uint32_t)v[u].z, (uint32_t)v[u].w};
+            m = max(m, absmax_bits8(w));
+        }
     }
-    if (a.q) store_rows(a, t, c);
-    if (a.qT) store_transposed(a, t, (int64_t)(tile / gx) * kTile, (int64_t)(tile % gx) * kTile, c, tq);
+    uint32_t w[8][4];
+    load_8x8<kSrcBf16>(a, t, w);
+    m = block_max(m, red);
+    const TensorScale sc = tensor_scale<FMT>(a, __uint_as_float(m << 16));
+    if (tile == 0 && threadIdx.x == 0 && a.scale) a.scale[0] = sc.s;
+    store_tensor_codes<FMT>(a, t, sc, (int64_t)(tile / gx) * kTile, (int64_t)(tile % gx) * kTile, w, tq);
 }
 
 // 1x128 row groups (q, scale) and/or 128x1 column groups (qT, scaleT) of the
@@ -731,20 +774,8 @@ __global__ __launch_bounds__(kThreads) void swiglu_bwd_pair_kernel(QuantArgs a, 
     } else {
         const TensorScale sc = tensor_scale<FMT>(a, tensor_amax(a, ps, red));
         if (bx == 0 && by == 0 && threadIdx.x == 0 && a.scale) a.scale[0] = sc.s;
-        auto half = [&](const Tile& th, const uint32_t w[8][4], int64_t col0) __attribute__((always_inline)) {
-            uint2 c[8];
-            if (sc.safe) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) c[i] = encode8<FMT, true>(w[i], sc.r);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) c[i] = encode8<FMT, false>(w[i], sc.r);
-            }
-            if (a.q) store_rows(a, th, c);
-            if (a.qT) store_transposed(a, th, by * kTile, col0, c, tq);
-        };
-        half(t, dg, bx * kTile);
-        half(tu, du, F + bx * kTile);
+        store_tensor_codes<FMT>(a, t, sc, by * kTile, bx * kTile, dg, tq);
+        store_tensor_codes<FMT>(a, tu, sc, by * kTile, F + bx * kTile, du, tq);
     }
 }
 
@@ -879,6 +910,14 @@ int64_t tiles_y(int64_t rows) { const int64_t g = (rows + kTile - 1) / kTile; re
 }  // namespace
 
 void launch_quantize_tensor(int fmt, QuantArgs a, void* ws, hipStream_t stream, bool swiglu) {
+    if (!swiglu && a.ld == a.cols && a.rows > 0 && a.cols > 0 && a.rows * a.cols <= kSmallTensor) {
+        const int64_t gx = tiles_x(a.cols);
+        const unsigned grid = (unsigned)(gx * tiles_y(a.rows));
+        a.supplied = 0;
+        if (fmt == kE4M3) quant_tensor_small_kernel<kE4M3><<<grid, kThreads, 0, stream>>>(a, (int)gx);
+        else quant_tensor_small_kernel<kE5M2><<<grid, kThreads, 0, stream>>>(a, (int)gx);
+        return;
+    }
     const int P = amax_num_partials(a.rows, a.cols);
     if (P > 0) launch_amax_partials(a.x, a.rows, a.cols, a.ld, reinterpret_cast<uint32_t*>(ws), P, stream, swiglu);
     amax_source(a, P, ws, stream);

@@ -90,6 +90,31 @@ def test_quantize_tensor_nonfinite(P, fmt):
             assert_bytes_equal(host(r["qT"]), qT, "qT %#x" % special)
 
 
+@pytest.mark.parametrize("fmt,rnd", [(E4, 0), (E5, 2)])
+@pytest.mark.parametrize("rows,cols,qT", [(16, 16, True), (1, 48, False), (77, 1536, False), (64, 2048, True),
+                                          (8192, 16, True), (80, 1648, True)])
+def test_quantize_tensor_one_launch(P, rows, cols, qT, fmt, rnd):
+    """Small dense tensors, which one launch reduces and encodes, up to the
+    largest (131072 elements) and just past it: equal to the oracle and to the
+    two-pass path (a padded row pitch takes it), the largest value in the last
+    element and an infinity or a NaN there too."""
+    import torch
+    for top in (None, 0x4640, 0x7F80, 0x7FC0):
+        x = inputs.case(rows + cols, (rows, cols), kind="outliers" if cols >= 100 else "normal")
+        if top is not None:
+            x[-1, -1] = top
+        q, _, s, _ = quant.quantize_tensor(x, OFMT[fmt], rule=RULE[rnd])
+        d = to_dev_bf16(x)
+        pad = torch.zeros(rows, cols + 8, dtype=torch.bfloat16, device="cuda")
+        pad[:, :cols] = d
+        for t in (d, pad[:, :cols]):
+            r = P.quantize_fp8(t, fmt, P.SCALE_TENSOR, rnd, want_q=True, want_qT=qT)
+            assert_bytes_equal(host(r["q"]), q, "q")
+            assert_f32_bits_equal(host(r["scale"]), np.array([s]), "scale")
+            if qT:
+                assert_bytes_equal(host(r["qT"]), q.T, "qT")
+
+
 def test_quantize_tensor_empty(P):
     x = np.zeros((0, 64), np.uint16)
     r = P.quantize_fp8(to_dev_bf16(x), E4, P.SCALE_TENSOR, 0, want_q=True)
