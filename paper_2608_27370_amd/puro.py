@@ -10,6 +10,7 @@ the GPU; 2-D with unit stride along rows.
 """
 
 import ctypes
+import functools
 import os
 from dataclasses import dataclass
 
@@ -115,11 +116,24 @@ def _check(fn, code):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# torch's raw handle of the current stream of a device, without the Stream
+# object that torch.cuda.current_stream() builds around it (2 us a call)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
+
+
+# Workspace sizes depend on the sizes alone; a program calls with few of them.
+@functools.lru_cache(maxsize=1024)
+def _size(fn, *args):
+    return getattr(lib(), fn)(*args)
 
 
 def _ld(t):
@@ -158,7 +172,7 @@ def quantize_fp8(x, fmt, mode=SCALE_TENSOR, rnd=SCALE_FP32, amax_in=None, want_q
     rows, cols = x.shape
     dev = x.device
     q, scale, qT, scaleT = _quant_outputs(rows, cols, mode, want_q, want_qT, out, dev)
-    w, nb = _ws(lib().puro_quantize_workspace_size(rows, cols), ws, dev)
+    w, nb = _ws(_size("puro_quantize_workspace_size", rows, cols), ws, dev)
     _check("puro_quantize_fp8", lib().puro_quantize_fp8(
         _ptr(x), rows, cols, _ld(x), fmt, mode, rnd, _ptr(amax_in), _ptr(q), _ptr(scale), _ptr(qT),
         _ptr(scaleT), _ptr(w), nb, _stream()))
@@ -181,7 +195,7 @@ def quantize_fp8_static(x, fmt, mode=SCALE_TENSOR, rnd=SCALE_FP32, amax_in=None,
 def _quant_outputs(rows, cols, mode, want_q, want_qT, out, dev):
     """Output tensors of a quantisation (supplied ones from `out` kept), in the
     scale layout the mode's SCALE_KMAJOR flag selects."""
-    out = dict(out or {})
+    out = out or {}
     G = 128
     km = bool(mode & SCALE_KMAJOR)
     base = mode & ~SCALE_KMAJOR
@@ -226,7 +240,7 @@ def swiglu_bwd_quantize_fp8(dh, gu, fmt, mode=SCALE_TENSOR, rnd=SCALE_FP32, want
     assert gu.shape[0] == rows and gu.shape[1] >= 2 * cols
     dev = dh.device
     q, scale, qT, scaleT = _quant_outputs(rows, 2 * cols, mode, want_q, want_qT, out, dev)
-    w, nb = _ws(lib().puro_swiglu_bwd_quantize_workspace_size(rows, cols), ws, dev)
+    w, nb = _ws(_size("puro_swiglu_bwd_quantize_workspace_size", rows, cols), ws, dev)
     _check("puro_swiglu_bwd_quantize_fp8", lib().puro_swiglu_bwd_quantize_fp8(
         _ptr(dh), _ld(dh), _ptr(gu), _ld(gu), rows, cols, fmt, mode, rnd, _ptr(q), _ptr(scale), _ptr(qT),
         _ptr(scaleT), _ptr(w), nb, _stream()))
@@ -245,7 +259,7 @@ def rmsnorm_quantize_fp8(x, gamma, eps, fmt, mode=SCALE_TENSOR, rnd=SCALE_FP32, 
     rstd = (out or {}).get("rstd")
     if rstd is None:
         rstd = torch.empty(rows, dtype=torch.float32, device=dev)
-    w, nb = _ws(lib().puro_rmsnorm_quantize_workspace_size(rows, cols), ws, dev)
+    w, nb = _ws(_size("puro_rmsnorm_quantize_workspace_size", rows, cols), ws, dev)
     _check("puro_rmsnorm_quantize_fp8", lib().puro_rmsnorm_quantize_fp8(
         _ptr(x), _ptr(gamma), rows, cols, _ld(x), float(eps), fmt, mode, rnd, _ptr(q), _ptr(scale), _ptr(qT),
         _ptr(scaleT), _ptr(rstd), _ptr(w), nb, _stream()))
@@ -262,7 +276,7 @@ def swiglu_quantize_fp8(gu, cols, fmt, mode=SCALE_TENSOR, rnd=SCALE_FP32, want_q
     assert gu.shape[1] >= 2 * cols
     dev = gu.device
     q, scale, qT, scaleT = _quant_outputs(rows, cols, mode, want_q, want_qT, out, dev)
-    w, nb = _ws(lib().puro_swiglu_quantize_workspace_size(rows, cols), ws, dev)
+    w, nb = _ws(_size("puro_swiglu_quantize_workspace_size", rows, cols), ws, dev)
     _check("puro_swiglu_quantize_fp8", lib().puro_swiglu_quantize_fp8(
         _ptr(gu), rows, cols, _ld(gu), fmt, mode, rnd, _ptr(q), _ptr(scale), _ptr(qT), _ptr(scaleT),
         _ptr(w), nb, _stream()))
@@ -278,7 +292,7 @@ def operand(data, fmt, mode, scale):
 
 
 def fp8_gemm_workspace_size(M, N, K, out_dtype):
-    return lib().puro_fp8_gemm_workspace_size(M, N, K, out_dtype)
+    return _size("puro_fp8_gemm_workspace_size", M, N, K, out_dtype)
 
 
 def fp8_gemm_plan(M, N, K, a_mode=SCALE_TENSOR, b_mode=SCALE_TENSOR):
@@ -327,13 +341,32 @@ class LinearRecipe:
     rnd: int = SCALE_FP32
 
     def c(self):
-        return Recipe(self.x_fmt, self.w_fmt, self.dy_fmt, self.blockwise, self.rnd)
+        return Recipe(*self.key())
+
+    def key(self):
+        return (self.x_fmt, self.w_fmt, self.dy_fmt, self.blockwise, self.rnd)
+
+
+@functools.lru_cache(maxsize=64)
+def _recipe_ref(key):
+    """The C recipe of a LinearRecipe's fields, by reference (read only)."""
+    return ctypes.byref(Recipe(*key))
+
+
+@functools.lru_cache(maxsize=1024)
+def _saved_sizes(M, N, K, key):
+    sizes = (_sz * 4)()
+    lib().puro_linear_saved_bytes(M, N, K, _recipe_ref(key), ctypes.byref(sizes))
+    return list(sizes)
+
+
+@functools.lru_cache(maxsize=1024)
+def _linear_size(fn, M, N, K, key):
+    return getattr(lib(), fn)(M, N, K, _recipe_ref(key))
 
 
 def linear_saved(M, N, K, recipe, device):
     """Allocate the saved-for-backward buffers of a linear layer."""
-    sizes = (_sz * 4)()
-    lib().puro_linear_saved_bytes(M, N, K, ctypes.byref(recipe.c()), ctypes.byref(sizes))
     G = 128
     xq_t = torch.empty(K, M, dtype=torch.uint8, device=device)
     wq_t = torch.empty(K, N, dtype=torch.uint8, device=device)
@@ -344,7 +377,7 @@ def linear_saved(M, N, K, recipe, device):
     else:
         xs = torch.empty(1, dtype=torch.float32, device=device)
         wsc = torch.empty(1, dtype=torch.float32, device=device)
-    assert [xq_t.numel(), xs.numel() * 4, wq_t.numel(), wsc.numel() * 4] == list(sizes)
+    assert [xq_t.numel(), xs.numel() * 4, wq_t.numel(), wsc.numel() * 4] == _saved_sizes(M, N, K, recipe.key())
     return dict(xq_t=xq_t, x_scale=xs, wq_t=wq_t, w_scale=wsc)
 
 
@@ -354,11 +387,11 @@ def _saved_struct(saved):
 
 
 def linear_fwd_workspace_size(M, N, K, recipe):
-    return lib().puro_linear_fwd_workspace_size(M, N, K, ctypes.byref(recipe.c()))
+    return _linear_size("puro_linear_fwd_workspace_size", M, N, K, recipe.key())
 
 
 def linear_bwd_workspace_size(M, N, K, recipe):
-    return lib().puro_linear_bwd_workspace_size(M, N, K, ctypes.byref(recipe.c()))
+    return _linear_size("puro_linear_bwd_workspace_size", M, N, K, recipe.key())
 
 
 def linear_fwd(X, W, recipe, Y=None, saved=None, ws=None):
@@ -372,7 +405,7 @@ def linear_fwd(X, W, recipe, Y=None, saved=None, ws=None):
         saved = linear_saved(M, N, K, recipe, dev)
     w, nb = _ws(linear_fwd_workspace_size(M, N, K, recipe), ws, dev)
     s = _saved_struct(saved)
-    _check("puro_linear_fwd", lib().puro_linear_fwd(_ptr(X), _ptr(W), M, N, K, ctypes.byref(recipe.c()),
+    _check("puro_linear_fwd", lib().puro_linear_fwd(_ptr(X), _ptr(W), M, N, K, _recipe_ref(recipe.key()),
                                                     _ptr(Y), ctypes.byref(s), _ptr(w), nb, _stream()))
     return Y, saved
 
@@ -389,7 +422,7 @@ def linear_bwd(dY, saved, recipe, K, want_dx=True, want_dw=True, dX=None, dW=Non
     w, nb = _ws(linear_bwd_workspace_size(M, N, K, recipe), ws, dev)
     s = _saved_struct(saved)
     _check("puro_linear_bwd", lib().puro_linear_bwd(
-        _ptr(dY), ctypes.byref(s), M, N, K, ctypes.byref(recipe.c()), _ptr(dX if want_dx else None),
+        _ptr(dY), ctypes.byref(s), M, N, K, _recipe_ref(recipe.key()), _ptr(dX if want_dx else None),
         _ptr(dW if want_dw else None), int(bool(accumulate_dw)), _ptr(w), nb, _stream()))
     return (dX if want_dx else None), (dW if want_dw else None)
 
