@@ -17,8 +17,14 @@
 //  * Within a slice the wave works in 64-byte k steps; the fragments of
 //    the next step are read from LDS into a second register set while the
 //    MFMAs of the current one run, and the DMA loads are spread between
-//    the MFMAs too. The loop body has no branches and waits on constant
-//    counts; one barrier per slice.
+//    the MFMAs of both steps: A's ring has spare units of 64 rows that take
+//    the next slice's first rows early. The loop body has no branches and
+//    waits on constant counts; one barrier per slice.
+//  * What bounds it: the long reductions run at 2.6 - 2.9 PFLOP/s, the clock
+//    held down by the matrix cores' power (gate/up Dgrad 16384x1536x17920 410
+//    -> 336 us over these steps: the spread loads 410 -> 385, the loop's
+//    arithmetic between the MFMAs 385 -> 338); at K 1536 a 256x256 tile spends
+//    a third of its time in prologue and epilogue (gate/up Fprop 471 -> 432).
 //  * LDS rows are XOR-swizzled in 16-byte chunks (conflict-free reads; the
 //    swizzle is applied on the global side because the DMA writes lane l at
 //    base + 16 l).
@@ -34,8 +40,10 @@
 //    to them) each own a contiguous range of tiles, grouped by row panels to
 //    share operand panels in that XCD's L2.
 //  * The epilogue stages each wave's FP32 tile in the idle ring and stores
-//    whole rows; interior tiles take a branch-free path that issues all LDS
-//    reads of a pass before its stores.
+//    whole rows; tiles inside the matrix, and edge tiles of whole 4-column
+//    vectors, take a branch-free path that issues all LDS reads of a group
+//    before its stores (before, edge tiles went element by element: quantise +
+//    GEMM with residual 3001x2056x2064 40 -> 35 us).
 //  * Small grids split K into ranges whose FP32 partial sums a second kernel
 //    adds in a fixed order (deterministic).
 
@@ -375,17 +383,11 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
     const v4i rb = make_rsrc(p.B + (int64_t)n0 * p.ldb, (uint32_t)(valid_n * p.ldb));
 
     // LDS layout of a slice: row r of a tile is SL bytes (CPR 16-byte chunks)
-    // and its logical chunk c sits at position c ^ key(r). The 16 (or 8)
-    // lanes of a ds_read_b128 phase read 16 (8) consecutive rows at the same
-    // logical chunk; the keys make them hit distinct banks with 64 (32)
-    // four-byte banks:
-    //  * SL = 64, key(r) = ((r >> 1) & 3) ^ ((r >> 3) & 1): of 16 consecutive
-    //    rows, those sharing a 64-byte position in a 256-byte bank line get
-    //    distinct keys, and so do those of 8 rows in a 128-byte line;
-    //  * SL = 128, key(r) = (r & 7) ^ ((r >> 3) & 1): of 16 consecutive rows
-    //    the 8 even (odd) ones, which share the lower (upper) half of a
-    //    256-byte bank line, get distinct keys, and 8 consecutive rows in a
-    //    128-byte line get the keys 0..7.
+    // and its logical chunk c sits at position c ^ key(r), key(r) = (r & 7) ^
+    // ((r >> 3) & 1). The 16 (or 8) lanes of a ds_read_b128 phase read 16 (8)
+    // consecutive rows at the same logical chunk: of 16 rows the 8 even (odd)
+    // ones, which share the lower (upper) half of a 256-byte bank line, get
+    // distinct keys, and 8 rows in a 128-byte line get the keys 0..7.
     // Lane l of a DMA load fills row RPL * blk + l / CPR at position l % CPR,
     // so it fetches the logical chunk (l % CPR) ^ key(row) of that row.
     auto row_key = [](int r) { return (r & 7) ^ ((r >> 3) & 1); };
