@@ -130,7 +130,12 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 // which cannot tell which LDS bytes a DMA writes, does not make every later
 // LDS read wait for it: the kernel waits explicitly (s_waitcnt vmcnt +
 // barrier) before reading a stage. One wait state separates the M0 write
-// from the DMA that reads it.
+// from the DMA that reads it. M0 is written without being saved and named as
+// a clobber, so that a value the compiler keeps there itself (an indexed
+// register move, an LDS builtin) is made again after it; saving it here would
+// cost two scalar moves per load.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"     // (M0 is a reserved register)
 template <int BYTES>
 __device__ __forceinline__ void dma_to_lds(v4i rsrc, uint32_t lds, uint32_t voff, uint32_t soff) {
     lds = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds);   // wave-uniform by construction
@@ -138,12 +143,13 @@ __device__ __forceinline__ void dma_to_lds(v4i rsrc, uint32_t lds, uint32_t voff
     if constexpr (BYTES == 16)
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                      "buffer_load_dwordx4 %1, %2, %3 offen lds"
-                     :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+                     :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
     else
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                      "buffer_load_dword %1, %2, %3 offen lds"
-                     :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+                     :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // dz's E4M3 copies from a wave's staged 128 x 128 BF16 tile (row r at
 // ep + 256 r, its 16-byte chunk c at position c ^ (r & 15)), for the LM

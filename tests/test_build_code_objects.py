@@ -1,4 +1,5 @@
-"""The built gfx950 code objects: no kernel keeps values in scratch memory.
+"""The built gfx950 code objects: no kernel keeps values in scratch memory, and
+what the GEMM's inline assembly relies on holds in every instance.
 
 A kernel whose accumulators or staged values spill to scratch still gives the
 right results, so no parity test notices, but it runs several times slower
@@ -24,24 +25,41 @@ LLVM = "/opt/rocm/llvm/bin"
 TARGET = "hipv4-amdgcn-amd-amdhsa--gfx950"
 
 
-def _kernels(obj):
-    """Metadata of every kernel in the gfx950 code object embedded in obj."""
+def _dump(obj, tool, *args):
+    """The output of an LLVM tool on the gfx950 code object embedded in obj."""
     with tempfile.TemporaryDirectory() as d:
         fat, co = os.path.join(d, "fatbin"), os.path.join(d, "co")
         subprocess.run([os.path.join(LLVM, "llvm-objcopy"), "--dump-section", ".hip_fatbin=" + fat, obj, os.devnull],
                        check=True, capture_output=True)
         subprocess.run([os.path.join(LLVM, "clang-offload-bundler"), "--unbundle", "--type=o", "--targets=" + TARGET,
                         "--input=" + fat, "--output=" + co], check=True, capture_output=True)
-        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", co], check=True,
-                               capture_output=True, text=True).stdout
+        return subprocess.run([os.path.join(LLVM, tool), *args, co], check=True, capture_output=True,
+                              text=True).stdout
+
+
+def _kernels(obj):
+    """Metadata of every kernel in the gfx950 code object embedded in obj."""
+    notes = _dump(obj, "llvm-readelf", "--notes")
     doc = re.search(r"^(amdhsa\..*?)^\s*\.\.\.\s*$", notes, re.S | re.M)
     assert doc, "no AMDGPU metadata in %s" % obj
     return yaml.safe_load(doc.group(1))["amdhsa.kernels"]
 
 
+def _listings(obj):
+    """(name, instructions) of every kernel in the gfx950 code object embedded in obj."""
+    out = []
+    for line in _dump(obj, "llvm-objdump", "-d", "--no-show-raw-insn").splitlines():
+        head = re.match(r"^[0-9a-f]+ <(.*)>:", line)
+        if head:
+            out.append((head.group(1), []))
+        elif out and line.strip():
+            out[-1][1].append(line.split("//")[0].strip())
+    return out
+
+
 def _objects():
     tools = all(os.access(os.path.join(LLVM, t), os.X_OK)
-                for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-readelf"))
+                for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-readelf", "llvm-objdump"))
     objs = [o for o in sorted(glob.glob(os.path.join(BUILD, "*.o"))) if not o.endswith("api.o")]
     if not tools or not objs:
         pytest.skip("needs the built objects (paper_2608_27370_amd/build.py) and the ROCm LLVM tools")
@@ -60,3 +78,24 @@ def test_no_kernel_uses_scratch():
                             k.get(".vgpr_spill_count"), k.get(".sgpr_spill_count")))
     assert seen > 100, "expected every GEMM and quantise instance, found %d kernels" % seen
     assert not bad, bad
+
+
+def test_m0_belongs_to_the_dma_loads():
+    """The LDS-DMA loads write M0 from inline assembly without saving it: each
+    such statement names it as a clobber, and the GEMM kernels use M0 for
+    nothing else."""
+    asm = []
+    for src in glob.glob(os.path.join(os.path.dirname(BUILD), "csrc", "*.h*")):
+        with open(src) as f:
+            asm += [a for a in re.findall(r"asm volatile\((.*?)\);", f.read(), re.S) if "m0, %" in a]
+    assert len(asm) == 2
+    for a in asm:
+        assert '"m0"' in a.rsplit(":", 1)[1], a
+    seen = 0
+    for obj in _objects():
+        if os.path.basename(obj).startswith("gemm_kernel"):
+            for name, ins in _listings(obj):
+                bad = [i for i in ins if re.search(r"\bm0\b", i) and not i.startswith("s_mov_b32 m0,")]
+                seen += len([i for i in ins if i.startswith("s_mov_b32 m0,")])
+                assert not bad, (name, bad[:4])
+    assert seen > 1000
