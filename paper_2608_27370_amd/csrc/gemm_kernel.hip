@@ -757,12 +757,17 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
         st = stn;
     }
     // the loads issued for slices past the end write zeros into the ring,
-    // which the epilogue reuses: let them land first
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // which the epilogue reuses: let them land first. And the last MFMA's
+    // results: a 16-pass matrix instruction's take 20 wait states to reach a
+    // VALU read, which the compiler does not insert before the reads in
+    // inline assembly below.
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 3" ::: "memory");
 
     // An accumulator read at its point of use (a copy the compiler may not
     // hoist): otherwise it moves accumulators to VGPRs ahead of the epilogue's
-    // branches, and spills.
+    // branches, and spills. (Volatile, so it stays behind the wait above, as
+    // that stays behind the MFMAs, each followed by a volatile statement on
+    // its result.)
     auto acc_at = [&](int i, int j, int e) __attribute__((always_inline)) {
         float v;
         asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(acc[i][j][e]));

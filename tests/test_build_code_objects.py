@@ -99,3 +99,27 @@ def test_m0_belongs_to_the_dma_loads():
                 seen += len([i for i in ins if i.startswith("s_mov_b32 m0,")])
                 assert not bad, (name, bad[:4])
     assert seen > 1000
+
+
+def test_accumulator_reads_wait_for_the_matrix_instructions():
+    """The epilogue reads accumulators in inline assembly, where the compiler
+    places no wait states for the matrix instruction that wrote them: between
+    a kernel's last MFMA and the first such read stand 20 explicit ones (16
+    passes and 4)."""
+    seen = 0
+    for obj in _objects():
+        if not os.path.basename(obj).startswith("gemm_kernel"):
+            continue
+        for name, ins in _listings(obj):
+            mfma = [i for i, x in enumerate(ins) if x.startswith("v_mfma")]
+            if not mfma:
+                continue
+            seen += 1
+            waits = 0
+            for x in ins[mfma[-1] + 1:]:
+                if x.startswith("s_nop"):
+                    waits += int(x.split()[1], 0) + 1
+                if x.startswith("v_accvgpr_read"):
+                    break
+            assert waits >= 20, (name, waits)
+    assert seen > 100
