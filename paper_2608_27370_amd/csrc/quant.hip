@@ -118,29 +118,22 @@ __global__ __launch_bounds__(kThreads) void amax_partial_kernel(AmaxJob j0, Amax
                 if constexpr (SRC == kSrcSwiglu) vu[u] = *reinterpret_cast<const uint4*>(p + 8 * cpr);
             }
         }
-        auto maxima = [&](auto near_c) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-                if constexpr (SRC == kSrcSwiglu) {
-                    const uint32_t wu[4] = {vu[u].x, vu[u].y, vu[u].z, vu[u].w};
-                    const uint32_t wg[4] = {w[0], w[1], w[2], w[3]};
-                    swiglu8<decltype(near_c)::value>(wg, wu, w);
-                }
-                m = max(m, absmax_bits8(w));
+        for (int u = 0; u < U; ++u) {
+            uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+            if constexpr (SRC == kSrcSwiglu) {
+                // eight elements at a time, as load_8x8 takes a row of them:
+                // with one choice for all U chunks the kernel took 157 VGPRs
+                // instead of 90, and a wave with one far gate the careful
+                // path for 64 elements of each lane (both passes of
+                // [8192, 8960] with N(0, 30) gates 190 us instead of 174)
+                const uint32_t wu[4] = {vu[u].x, vu[u].y, vu[u].z, vu[u].w};
+                const uint32_t wg[4] = {w[0], w[1], w[2], w[3]};
+                if (wave_none(absmax_bits8(wg) > kNearGateBits)) swiglu8<true>(wg, wu, w);
+                else swiglu8<false>(wg, wu, w);
+                __builtin_amdgcn_sched_barrier(0);
             }
-        };
-        if constexpr (SRC == kSrcSwiglu) {
-            uint32_t gm = 0;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-                gm = max(gm, absmax_bits8(w));
-            }
-            if (wave_none(gm > kNearGateBits)) maxima(std::true_type{});
-            else maxima(std::false_type{});
-        } else {
-            maxima(std::true_type{});
+            m = max(m, absmax_bits8(w));
         }
     }
     m = block_max(m, red);
