@@ -156,6 +156,36 @@ def test_group_exponent_edges(P, fmt, rnd):
     assert_f32_bits_equal(host(r["scaleT"]), sT, "col scaleT")
 
 
+@pytest.mark.parametrize("fmt", [E4, E5])
+@pytest.mark.parametrize("turned", [False, True], ids=["rows", "columns"])
+def test_floor_rule_clipped_groups(P, fmt, turned):
+    """Waves whose groups are all finite and above the exponent clamp, some of
+    them clipped by the floor rule (significand above 1.75) and some not: the
+    groups' exponents run over the whole range, one row (or column) after the
+    other, with values down to zeros of both signs and subnormals in each."""
+    rng = np.random.default_rng(fmt)
+    least = ((8 if fmt == E4 else 15) + 1) << 7
+    x = np.zeros((128, 256), np.uint16)
+    for i in range(128):
+        top = (least + (0x7F00 - least) * i // 127) // 128 * 128 + (0x60, 0x61, 0x7F, 0x00)[i % 4]
+        x[i] = rng.integers(0, top + 1, 256)
+        x[i, 5::16] = top - rng.integers(0, 0x300, 16)
+        x[i, [i, 255 - i]] = top
+        x[i, [(i + 1) % 128, 130]] = 0
+    x |= (rng.integers(0, 2, x.shape) << 15).astype(np.uint16)
+    if turned:
+        x = np.ascontiguousarray(x.T)
+    q, s = quant.quantize_rows_1x128(x, OFMT[fmt], RULE[2])
+    qT, sT = quant.quantize_cols_128x1(x, OFMT[fmt], RULE[2])
+    for mode in (P.SCALE_ROW_1x128, P.SCALE_COL_128x1):
+        r = P.quantize_fp8(to_dev_bf16(x), fmt, mode, 2, want_q=True, want_qT=True)
+        if mode == P.SCALE_ROW_1x128:
+            assert_bytes_equal(host(r["q"]), q, "row q")
+            assert_f32_bits_equal(host(r["scale"]), s, "row scale")
+        assert_bytes_equal(host(r["qT"]), qT, "col qT")
+        assert_f32_bits_equal(host(r["scaleT"]), sT, "col scaleT")
+
+
 @pytest.mark.parametrize("rnd", [1, 2], ids=["pow2", "pow2_floor"])
 @pytest.mark.parametrize("fmt", [E4, E5])
 @pytest.mark.parametrize("shape,kind,specials", [((256, 384), "normal", False), ((128, 128), "student_t", False),
@@ -188,6 +218,36 @@ def test_quantize_rows_and_columns(P, fmt, shape, kind, specials, rnd):
     r = P.quantize_fp8(d, fmt, P.SCALE_COL_128x1 | P.SCALE_KMAJOR, rnd)
     assert_bytes_equal(host(r["qT"]), qT, "col qT only (k-major)")
     assert_f32_bits_equal(host(r["scaleT"]), sT.T, "col scaleT only (k-major)")
+
+
+@pytest.mark.parametrize("fmt", [E4, E5])
+@pytest.mark.parametrize("turned", [False, True], ids=["rows", "columns"])
+def test_floor_rule_clipped_groups(P, fmt, turned):
+    """Waves whose groups are all finite and above the exponent clamp, some of
+    them clipped by the floor rule (significand above 1.75) and some not: the
+    groups' exponents run over the whole range, one row (or column) after the
+    other, with values down to zeros of both signs and subnormals in each."""
+    rng = np.random.default_rng(fmt)
+    least = ((8 if fmt == E4 else 15) + 1) << 7
+    x = np.zeros((128, 256), np.uint16)
+    for i in range(128):
+        top = (least + (0x7F00 - least) * i // 127) // 128 * 128 + (0x60, 0x61, 0x7F, 0x00)[i % 4]
+        x[i] = rng.integers(0, top + 1, 256)
+        x[i, 5::16] = top - rng.integers(0, 0x300, 16)
+        x[i, [i, 255 - i]] = top
+        x[i, [(i + 1) % 128, 130]] = 0
+    x |= (rng.integers(0, 2, x.shape) << 15).astype(np.uint16)
+    if turned:
+        x = np.ascontiguousarray(x.T)
+    q, s = quant.quantize_rows_1x128(x, OFMT[fmt], RULE[2])
+    qT, sT = quant.quantize_cols_128x1(x, OFMT[fmt], RULE[2])
+    for mode in (P.SCALE_ROW_1x128, P.SCALE_COL_128x1):
+        r = P.quantize_fp8(to_dev_bf16(x), fmt, mode, 2, want_q=True, want_qT=True)
+        if mode == P.SCALE_ROW_1x128:
+            assert_bytes_equal(host(r["q"]), q, "row q")
+            assert_f32_bits_equal(host(r["scale"]), s, "row scale")
+        assert_bytes_equal(host(r["qT"]), qT, "col qT")
+        assert_f32_bits_equal(host(r["scaleT"]), sT, "col scaleT")
 
 
 @pytest.mark.parametrize("rnd", [1, 2], ids=["pow2", "pow2_floor"])
