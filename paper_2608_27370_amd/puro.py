@@ -131,7 +131,8 @@ def _stream():
 
 
 # Workspace sizes depend on the sizes alone; a program calls with few of them.
-@functools.lru_cache(maxsize=1024)
+# (typed: 1, 1.0 and True are different arguments to ctypes, which refuses 1.0)
+@functools.lru_cache(maxsize=1024, typed=True)
 def _size(fn, *args):
     return getattr(lib(), fn)(*args)
 
@@ -195,7 +196,7 @@ def quantize_fp8_static(x, fmt, mode=SCALE_TENSOR, rnd=SCALE_FP32, amax_in=None,
 def _quant_outputs(rows, cols, mode, want_q, want_qT, out, dev):
     """Output tensors of a quantisation (supplied ones from `out` kept), in the
     scale layout the mode's SCALE_KMAJOR flag selects."""
-    out = out or {}
+    out = dict(out) if out else {}
     G = 128
     km = bool(mode & SCALE_KMAJOR)
     base = mode & ~SCALE_KMAJOR
@@ -347,22 +348,22 @@ class LinearRecipe:
         return (self.x_fmt, self.w_fmt, self.dy_fmt, self.blockwise, self.rnd)
 
 
-@functools.lru_cache(maxsize=64)
-def _recipe_ref(key):
+@functools.lru_cache(maxsize=64, typed=True)
+def _recipe_ref(*key):
     """The C recipe of a LinearRecipe's fields, by reference (read only)."""
     return ctypes.byref(Recipe(*key))
 
 
-@functools.lru_cache(maxsize=1024)
-def _saved_sizes(M, N, K, key):
+@functools.lru_cache(maxsize=1024, typed=True)
+def _saved_sizes(M, N, K, *key):
     sizes = (_sz * 4)()
-    lib().puro_linear_saved_bytes(M, N, K, _recipe_ref(key), ctypes.byref(sizes))
+    lib().puro_linear_saved_bytes(M, N, K, _recipe_ref(*key), ctypes.byref(sizes))
     return list(sizes)
 
 
-@functools.lru_cache(maxsize=1024)
-def _linear_size(fn, M, N, K, key):
-    return getattr(lib(), fn)(M, N, K, _recipe_ref(key))
+@functools.lru_cache(maxsize=1024, typed=True)
+def _linear_size(fn, M, N, K, *key):
+    return getattr(lib(), fn)(M, N, K, _recipe_ref(*key))
 
 
 def linear_saved(M, N, K, recipe, device):
@@ -377,7 +378,7 @@ def linear_saved(M, N, K, recipe, device):
     else:
         xs = torch.empty(1, dtype=torch.float32, device=device)
         wsc = torch.empty(1, dtype=torch.float32, device=device)
-    assert [xq_t.numel(), xs.numel() * 4, wq_t.numel(), wsc.numel() * 4] == _saved_sizes(M, N, K, recipe.key())
+    assert [xq_t.numel(), xs.numel() * 4, wq_t.numel(), wsc.numel() * 4] == _saved_sizes(M, N, K, *recipe.key())
     return dict(xq_t=xq_t, x_scale=xs, wq_t=wq_t, w_scale=wsc)
 
 
@@ -387,11 +388,11 @@ def _saved_struct(saved):
 
 
 def linear_fwd_workspace_size(M, N, K, recipe):
-    return _linear_size("puro_linear_fwd_workspace_size", M, N, K, recipe.key())
+    return _linear_size("puro_linear_fwd_workspace_size", M, N, K, *recipe.key())
 
 
 def linear_bwd_workspace_size(M, N, K, recipe):
-    return _linear_size("puro_linear_bwd_workspace_size", M, N, K, recipe.key())
+    return _linear_size("puro_linear_bwd_workspace_size", M, N, K, *recipe.key())
 
 
 def linear_fwd(X, W, recipe, Y=None, saved=None, ws=None):
@@ -405,7 +406,7 @@ def linear_fwd(X, W, recipe, Y=None, saved=None, ws=None):
         saved = linear_saved(M, N, K, recipe, dev)
     w, nb = _ws(linear_fwd_workspace_size(M, N, K, recipe), ws, dev)
     s = _saved_struct(saved)
-    _check("puro_linear_fwd", lib().puro_linear_fwd(_ptr(X), _ptr(W), M, N, K, _recipe_ref(recipe.key()),
+    _check("puro_linear_fwd", lib().puro_linear_fwd(_ptr(X), _ptr(W), M, N, K, _recipe_ref(*recipe.key()),
                                                     _ptr(Y), ctypes.byref(s), _ptr(w), nb, _stream()))
     return Y, saved
 
@@ -422,7 +423,7 @@ def linear_bwd(dY, saved, recipe, K, want_dx=True, want_dw=True, dX=None, dW=Non
     w, nb = _ws(linear_bwd_workspace_size(M, N, K, recipe), ws, dev)
     s = _saved_struct(saved)
     _check("puro_linear_bwd", lib().puro_linear_bwd(
-        _ptr(dY), ctypes.byref(s), M, N, K, _recipe_ref(recipe.key()), _ptr(dX if want_dx else None),
+        _ptr(dY), ctypes.byref(s), M, N, K, _recipe_ref(*recipe.key()), _ptr(dX if want_dx else None),
         _ptr(dW if want_dw else None), int(bool(accumulate_dw)), _ptr(w), nb, _stream()))
     return (dX if want_dx else None), (dW if want_dw else None)
 

@@ -207,6 +207,24 @@ def test_gemm_plan_covers_every_configuration(puro, modes):
         assert p["splits"] > 1 and p["launches"] == 2 and p["stages"] == stages, (shape, p)
 
 
+def test_remembered_sizes_keep_the_argument_checks(puro):
+    """The binding's remembered sizes and recipes are told apart by type as
+    well: a float equal to a remembered integer is refused as ctypes refuses
+    it, whatever was called before. And `out` may be any mapping or pairs."""
+    assert puro.fp8_gemm_workspace_size(128, 128, 8192, 1) > 0
+    with pytest.raises(ctypes.ArgumentError):
+        puro.fp8_gemm_workspace_size(128.0, 128, 8192, 1)
+    good, odd = puro.LinearRecipe(0, 0, 0, 1, 1), puro.LinearRecipe(0, 0, 0, 1, 1.0)
+    assert puro.linear_fwd_workspace_size(256, 256, 256, good) > 0
+    assert puro.linear_saved(256, 256, 256, good, "cpu")["xq_t"].shape == (256, 256)
+    for call in (lambda: puro.linear_fwd_workspace_size(256, 256, 256, odd),
+                 lambda: puro.linear_saved(256, 256, 256, odd, "cpu")):
+        with pytest.raises(TypeError):
+            call()
+    q = object()
+    assert puro._quant_outputs(16, 16, 0, True, False, [("q", q)], "cpu")[0] is q
+
+
 def test_gemm_plan_validation(puro):
     L = puro.lib()
     assert L.puro_fp8_gemm_plan(-1, 16, 16, 0, 0, None, None, None, None, None) == ERR_SHAPE
