@@ -143,9 +143,13 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, bool grouped, int batch = 1, boo
     constexpr int kEntries = 256;
     static thread_local Entry table[kEntries];
     const int flags = 4 | (grouped ? 1 : 0) | (upper ? 2 : 0);
-    const uint64_t h = ((uint64_t)M * 0x9E3779B97F4A7C15ull) ^ ((uint64_t)N * 0xC2B2AE3D27D4EB4Full) ^
-                       ((uint64_t)K * 0x165667B19E3779F9ull) ^ ((uint64_t)batch << 8) ^ (uint64_t)flags;
-    Entry& e = table[(h ^ (h >> 29)) % kEntries];
+    // multiplicative hashing (Knuth, vol. 3, 6.4): 2^64 over the golden ratio,
+    // the top bits of the product
+    constexpr uint64_t kGolden = 0x9E3779B97F4A7C15ull;
+    uint64_t h = (uint64_t)(batch * 8 + flags);
+    for (const int64_t v : {M, N, K}) h = (h * kGolden) ^ (uint64_t)v;
+    Entry& e = table[(h * kGolden) >> 56];
+    static_assert(kEntries == 256, "8 bits of the hash");
     if (e.flags != flags || e.M != M || e.N != N || e.K != K || e.batch != batch)
         e = Entry{M, N, K, batch, flags, search_plan(M, N, K, grouped, batch, upper)};
     return e.plan;
