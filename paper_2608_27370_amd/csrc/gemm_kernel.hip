@@ -90,6 +90,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 // BF16 outputs of FP8 operands are a linear layer's: far larger than the L2
 // and next read by another kernel, they are stored past the caches
 // (non-temporal). Those of BF16 operands, MuonH's, are read back at once.
+// (Binary32 outputs of FP8 operands are both a Wgrad's, read later, and the
+// LM head's dX accumulator, read back by the next chunk: Params::nt_f32.)
 template <int FA> constexpr bool kStreamOut = FA != kBF16;
 
 constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }
@@ -1263,8 +1265,12 @@ __global__ __launch_bounds__(WM * WN * 64 * (PROD ? 2 : 1)) void gemm_fp8_kernel
                             }
                         }
                     };
-                    if (OUT != 2 && p.nt_out) store_group(std::true_type{});
-                    else store_group(std::false_type{});
+                    if constexpr (ES == 2) {
+                        store_group(std::bool_constant<kStreamOut<FA>>{});
+                    } else {
+                        if (OUT != 2 && p.nt_f32) store_group(std::true_type{});
+                        else store_group(std::false_type{});
+                    }
                 }
             };
             auto run = [&](auto edge_c) __attribute__((always_inline)) {

@@ -140,9 +140,10 @@ struct GemmProblem {
     // above the diagonal (square tiles); the tiles below are left unwritten
     // (gemm_tile returns the tile edge for filling them in)
     int upper = 0;
-    // D is not read back soon: interior tiles store it with non-temporal
-    // (streaming) stores, which shorten the output-heavy epilogues
-    int nt_out = 0;
+    // a binary32 D is not read back soon: store it with non-temporal
+    // (streaming) stores, which shorten the output-heavy epilogues (a BF16 D
+    // is streamed or not by the operands' format, in every tile)
+    int nt_f32 = 0;
     // `batch` independent problems of the same shape and scales: operand,
     // output and residual b start bsa, bsb, bsd, bsr elements after those of
     // problem 0

@@ -123,3 +123,25 @@ def test_accumulator_reads_wait_for_the_matrix_instructions():
                     break
             assert waits >= 20, (name, waits)
     assert seen > 100
+
+
+def test_bf16_outputs_stream_by_operand_format():
+    """The BF16 outputs of FP8 operands leave by non-temporal stores in every
+    store path of a tile, those of BF16 operands in none."""
+    seen = 0
+    for obj in _objects():
+        if not os.path.basename(obj).startswith("gemm_kernel"):
+            continue
+        for name, ins in _listings(obj):
+            # template arguments: tile (2), wave grid (2), operand formats (2), output kind
+            t = re.search(r"gemm_fp8_kernelI((?:Li\d+E){7})", name)
+            if not t:
+                continue
+            fa, _, out = [int(v) for v in re.findall(r"\d+", t.group(1))][4:]
+            if out not in (0, 3):          # BF16, alone or with bias / residual
+                continue
+            seen += 1
+            stores = [i for i in ins if i.startswith("buffer_store")]
+            streamed = [i for i in stores if re.search(r"\bnt\b", i)]
+            assert stores and len(streamed) == (0 if fa == 2 else len(stores)), (name, len(stores), len(streamed))
+    assert seen > 100
