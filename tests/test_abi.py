@@ -207,6 +207,21 @@ def test_gemm_plan_covers_every_configuration(puro, modes):
         assert p["splits"] > 1 and p["launches"] == 2 and p["stages"] == stages, (shape, p)
 
 
+# The same with edge tiles, and the configurations for few rows and for grids of
+# about one tile per CU (tests/test_gpu_gemm.py runs these shapes too).
+EDGE_PLAN_SHAPES = {(64, 64, 8): (77, 2060, 1536), (256, 128, 2): (1934, 3732, 2048), (256, 256, 2): (3086, 3732, 256),
+                    (256, 192, 2): (2318, 3356, 256), (128, 128, 4): (590, 628, 1024), (128, 128, 2): (590, 636, 256)}
+
+
+@pytest.mark.parametrize("modes", [(0, 0), (1, 3), (1, 1)], ids=["tensor", "row-block", "row-row"])
+def test_gemm_plan_covers_every_configuration_at_edges(puro, modes):
+    for cfg, (M, N, K) in EDGE_PLAN_SHAPES.items():
+        p = puro.fp8_gemm_plan(M, N, K + (16 if modes == (0, 0) else 0), *modes)
+        assert (p["tile_m"], p["tile_n"], p["stages"]) == cfg, ((M, N, K), p)
+        assert p["splits"] == 1 and p["launches"] == 1
+        assert M % cfg[0] and N % cfg[1]
+
+
 def test_remembered_sizes_keep_the_argument_checks(puro):
     """The binding's remembered sizes and recipes are told apart by type as
     well: a float equal to a remembered integer is refused as ctypes refuses

@@ -382,6 +382,58 @@ def test_gemm_256x128_tiles(P, shape, scales):
     check_bf16(bf16_bits(D)[ms, ns], ref, den, what=what + " epilogue", slack=slack)
 
 
+# Tiles that end inside the matrix's last rows and columns, on each of the
+# larger configurations: rows ending inside a 32-row fragment with the last
+# wave tile wholly or partly outside, columns ending inside one (N % 8 == 4)
+# and (per-tensor) a k tail. (M, N, K without the tail, tile, ring depth)
+RAGGED_TILE_CASES = [(3086, 3732, 256, 256, 256, 2), (2318, 3356, 256, 256, 192, 2), (590, 636, 256, 128, 128, 2),
+                     (590, 628, 1024, 128, 128, 4), (1934, 3732, 2048, 256, 128, 2)]
+
+
+@pytest.mark.parametrize("case", RAGGED_TILE_CASES, ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("scales", ["tensor", "row-block", "row-row"])
+def test_gemm_ragged_tiles(P, case, scales):
+    """Every output kind of the edge tiles' stores: BF16, binary32, binary32
+    added to D, bias plus residual (apart and in place), and for block scales
+    both scale layouts; 16 entries of every 256x256 block and the whole first
+    and last blocks."""
+    from gpu_util import sample_entries
+    M, N, K, tm, tn, st = case
+    am, bm = ("tensor", "tensor") if scales == "tensor" else scales.split("-")
+    if scales == "tensor":
+        K += 16
+        a, sa = _operand_tensor(81, M, K, E4)
+        b, sb = _operand_tensor(82, N, K, E4, std=0.02)
+    else:
+        a, sa = _operand_grouped(81, M, K, E4, am)
+        b, sb = _operand_grouped(82, N, K, E4, bm, std=0.02)
+    plan = P.fp8_gemm_plan(M, N, K, MODE[am], MODE[bm])
+    assert (plan["tile_m"], plan["tile_n"], plan["stages"], plan["splits"]) == (tm, tn, st, 1), plan
+    op = (a, fp8.E4M3, sa, am, b, fp8.E4M3, sb, bm)
+    ms, ns = sample_entries(M, N, np.random.default_rng(83))
+    ref, den = gemm.gemm_entries(ms, ns, *op)
+    slack = mfma_model.truncation_loss(ms, ns, *op)
+    what = "ragged %s %s" % (scales, case)
+    d16 = bf16_bits(_run(P, a, E4, sa, am, b, E4, sb, bm, 0))
+    check_bf16(d16[ms, ns], ref, den, what=what, slack=slack)
+    check_fp32(host(_run(P, a, E4, sa, am, b, E4, sb, bm, 1))[ms, ns], ref, den, what=what, slack=slack)
+    D0 = np.random.default_rng(84).standard_normal((M, N)).astype(np.float32)
+    old = D0[ms, ns].astype(np.float64)
+    D = host(_run(P, a, E4, sa, am, b, E4, sb, bm, 1, D0=D0))
+    # the old value enters the binary32 sum exactly; its own rounding adds |old| * 2**-24
+    check_fp32(D[ms, ns], ref + old, den + np.abs(old) * 2.0 ** -24 / 1e-5, what=what + " accumulate", slack=slack)
+    bias, resid = _epilogue_terms(85, M, N, True, True)
+    eref, eden = gemm.epilogue(ref, den, bf16.to_f32(bias)[ns], bf16.to_f32(resid)[ms, ns])
+    for in_place in (False, True):
+        D = _run_epi(P, a, E4, sa, am, b, E4, sb, bm, bias, resid, in_place=in_place)
+        check_bf16(bf16_bits(D)[ms, ns], eref, eden, what=what + " epilogue", slack=slack)
+    if scales != "tensor":
+        da, db = to_dev(a), to_dev(b)
+        km = P.fp8_gemm(P.operand(da, E4, MODE[am] | P.SCALE_KMAJOR, to_dev(np.ascontiguousarray(sa.T))), M,
+                        P.operand(db, E4, MODE[bm] | P.SCALE_KMAJOR, to_dev(np.ascontiguousarray(sb.T))), N, K, 0)
+        assert np.array_equal(bf16_bits(km), d16), what + " k-major scales"
+
+
 # The epilogue on the tile configurations the shapes above do not reach:
 # 256x256 (the one-pass BF16 staging, whose residual block arrives in LDS by
 # DMA before the tile's stores: here in place on D), 256x192 (bias repeating
