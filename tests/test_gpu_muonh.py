@@ -101,6 +101,24 @@ def test_newton_schulz_one_step(P, r, c, count):
         X = np.stack([muonh.ns_step_bf16(X[i])[2] for i in range(count)])
 
 
+@pytest.mark.timeout(300)
+def test_newton_schulz_batch_of_ragged_large_tiles(P):
+    """A batch whose symmetric products take 256x256 tiles (20 matrices of 896
+    rows: 200 tiles of 256, 560 of 128) though its rows end inside the last of
+    them; the first and last matrices in the band."""
+    r, count = 896, 20
+    rng = np.random.default_rng(7)
+    X = bf16.from_f64_rne(rng.standard_normal((count, r, r)).astype(np.float32).astype(np.float64) / r)
+    for i in (0, count - 1):
+        X[i] = muonh.ns_start_bf16(inputs.muonh_matrix(r, r, key=150 + i)[1])
+    print("newton-schulz: GPU step of %d [%d, %d]" % (count, r, r), flush=True)
+    got = bf16_bits(P.newton_schulz_bf16(to_dev_bf16(X), steps=1))
+    for i in (0, count - 1):
+        lo, hi = ns_step_band(X[i])
+        ok = in_band(got[i], lo, hi)
+        assert ok.all(), "matrix %d: %d outside the band" % (i, (~ok).sum())
+
+
 def _run_step(P, W, G, buf, R, eta, steps, mu=0.95):
     torch = __import__("torch")
     Wd, Gd, bd = to_dev(W), to_dev(G), to_dev(buf)
