@@ -156,6 +156,20 @@ def test_group_exponent_edges(P, fmt, rnd):
     assert_f32_bits_equal(host(r["scaleT"]), sT, "col scaleT")
 
 
+@pytest.mark.parametrize("rows,cols", [(1, 131072), (1, 131088), (3, 43680), (16, 8192), (16, 8208)])
+def test_quantize_tensor_one_launch_short_and_wide(P, rows, cols):
+    """Few rows and many tiles on both sides of the one-launch limit, the
+    largest value in the last element."""
+    x = inputs.case(rows + cols, (rows, cols))
+    x[-1, -1] = 0x4640
+    q, _, s, _ = quant.quantize_tensor(x, OFMT[E4], rule=RULE[0])
+    r = P.quantize_fp8(to_dev_bf16(x), E4, P.SCALE_TENSOR, 0, want_q=True, want_qT=rows % 16 == 0)
+    assert_bytes_equal(host(r["q"]), q, "q")
+    assert_f32_bits_equal(host(r["scale"]), np.array([s]), "scale")
+    if rows % 16 == 0:
+        assert_bytes_equal(host(r["qT"]), q.T, "qT")
+
+
 @pytest.mark.parametrize("fmt", [E4, E5])
 @pytest.mark.parametrize("turned", [False, True], ids=["rows", "columns"])
 def test_floor_rule_clipped_groups(P, fmt, turned):
