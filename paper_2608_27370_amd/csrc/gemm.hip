@@ -119,7 +119,7 @@ Plan search_plan(int64_t M, int64_t N, int64_t K, bool grouped, int batch, bool 
             const int64_t full = units / slots, rem = units - full * slots;
             const double waves = full + (rem == 0 ? 0.0 : upper && full > 0 && slots > kCUs && rem <= kCUs ? 0.7 : 1.0);
             const double busy = units < slots ? (double)units / slots : 1.0;
-            double cost = waves * (t.fixed_us + t.slice_us * (kps > 0 ? kps : 1) * (1.0 - 0.378 * (1.0 - busy)));
+            double cost = waves * (t.fixed_us + t.slice_us * (grouped ? t.grouped : 1.0f) * (kps > 0 ? kps : 1) * (1.0 - 0.378 * (1.0 - busy)));
             if (splits > 1) cost += 1.784 + 0.2525e-6 * splits * (double)M * N * 4.0 * batch;
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;

@@ -81,7 +81,8 @@ struct TileCfg {
     int xa;              // spare 64-row units of the A ring (fewer where LDS lacks room for them)
     int prod;            // producer waves issue the global->LDS loads
     float fixed_us;      // time model: per wave of work units ...
-    float slice_us;      // ... plus per k slice of a unit (MI355X, all CUs busy)
+    float slice_us;      // ... plus per k slice of a unit (MI355X, all CUs busy),
+    float grouped;       // times this with block scales
 };
 // Four MFMA waves (one per SIMD) in a 2x2 grid. The large wave tiles need
 // the least LDS traffic per MFMA (128x128: 16 MFMAs per 16 KB of fragment
@@ -104,14 +105,21 @@ struct TileCfg {
 // configuration and split) of 44 shapes, per-tensor and block-scaled, from 16
 // to 16384 rows: the choice is within 0.3% of the best of them on average, 12%
 // at most (2304x2048x1024 at 10.9 us).
+// Block scales lengthen a slice by what the scales' loads and conversion add
+// beside its MFMAs: 1.02 - 1.07 (256x256, measured from K 4096 to 8192 on grids
+// of 16 to 256 tiles), 1.06 - 1.14 (256x192), 1.2 - 1.5 and 1.0 - 1.25 (128x128,
+// 4- and 2-deep), 1.0 - 1.15 (64x64), 1.1 - 1.35 (256x128), more where both
+// operands have a scale per row. Without the factor long reductions stayed
+// unsplit that are faster split: 973x1240x4736 24.3 us against 19.1,
+// 283x3548x4096 23.5 against 17.3.
 #define PURO_TILE_LIST(X)                                  \
-    X(0, 256, 256, 2, 2, 128, 2, 4, 0, 9.276f, 1.343f)     \
-    X(1, 256, 192, 2, 2, 128, 2, 4, 0, 9.429f, 0.990f)     \
-    X(2, 128, 128, 2, 2, 128, 4, 0, 1, 6.424f, 0.3645f)    \
-    X(3, 128, 128, 2, 2, 128, 2, 0, 0, 4.071f, 0.8992f)    \
-    X(4, 64, 64, 2, 2, 128, 8, 0, 0, 3.031f, 0.2984f)      \
-    X(5, 256, 128, 2, 2, 128, 2, 3, 0, 6.577f, 0.7372f)
-#define PURO_TILE_ROW(i, bm, bn, wm, wn, sl, nst, xa, prod, f, s) {bm, bn, wm, wn, sl, nst, xa, prod, f, s},
+    X(0, 256, 256, 2, 2, 128, 2, 4, 0, 9.276f, 1.343f, 1.05f)     \
+    X(1, 256, 192, 2, 2, 128, 2, 4, 0, 9.429f, 0.990f, 1.10f)     \
+    X(2, 128, 128, 2, 2, 128, 4, 0, 1, 6.424f, 0.3645f, 1.40f)    \
+    X(3, 128, 128, 2, 2, 128, 2, 0, 0, 4.071f, 0.8992f, 1.30f)    \
+    X(4, 64, 64, 2, 2, 128, 8, 0, 0, 3.031f, 0.2984f, 1.20f)      \
+    X(5, 256, 128, 2, 2, 128, 2, 3, 0, 6.577f, 0.7372f, 1.20f)
+#define PURO_TILE_ROW(i, bm, bn, wm, wn, sl, nst, xa, prod, f, s, g) {bm, bn, wm, wn, sl, nst, xa, prod, f, s, g},
 
 constexpr int kLdsBytes = 160 * 1024;
 // LDS bytes of a configuration with xa spare A units, and the spare units

@@ -1368,7 +1368,7 @@ void launch_tile(const Params& prm, int out, int grid, hipStream_t stream) {
 
 template <int FA, int FB, bool GROUPED>
 void launch_variant(const Params& prm, int cfg, int out, int grid, hipStream_t stream) {
-#define PURO_TILE_CASE(i, bm, bn, wm, wn, sl, nst, xa, prod, f, s) \
+#define PURO_TILE_CASE(i, bm, bn, wm, wn, sl, nst, xa, prod, f, s, g) \
     case i: launch_tile<bm, bn, wm, wn, sl, nst, xa, prod, FA, FB, GROUPED>(prm, out, grid, stream); break;
     switch (cfg) { PURO_TILE_LIST(PURO_TILE_CASE) }
 #undef PURO_TILE_CASE

@@ -222,6 +222,14 @@ def test_gemm_plan_covers_every_configuration_at_edges(puro, modes):
         assert M % cfg[0] and N % cfg[1]
 
 
+@pytest.mark.parametrize("shape", [(973, 1240, 4736), (283, 3548, 4096), (2552, 580, 4864), (3546, 448, 4352)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_gemm_plan_splits_long_block_scaled_reductions(puro, shape):
+    """Block scales make a slice of the 128x128 tiles up to half again as long,
+    so these reductions are faster split than left to 80 - 140 workgroups."""
+    assert puro.fp8_gemm_plan(*shape, 1, 1)["splits"] > 1
+
+
 def test_remembered_sizes_keep_the_argument_checks(puro):
     """The binding's remembered sizes and recipes are told apart by type as
     well: a float equal to a remembered integer is refused as ctypes refuses
