@@ -82,9 +82,14 @@ int per_cu(const TileCfg& t, bool grouped) {
 }
 
 // Whether a problem may take the 64x64 tiles: few rows or columns, and at
-// least 24 tiles. Above 512 rows the 128x128 tiles fill enough of the chip
-// (700x2048x2048: 9.8 against 12.6 us); below 24 tiles splitting k over the
-// 128x128 ones keeps more CUs busy. Measured for single problems only.
+// least 24 tiles; single problems only (batches were not measured). Measured
+// against the plan without them, forced: up to one wave of tiles (one per CU)
+// they are faster also at 513 to 1024 rows (640x1536x1536 7.1 against 8.0 us,
+// 1024x1024x2048 7.7 against 9.0), beyond that slower by 40% and more
+// (513x2048x1536 11.6 against 8.1, 1024x2048x1536 12.3 against 8.4). Below 24
+// tiles they win as well where the reduction is short (20x1376x1280 6.0
+// against 6.9). Both limits stand where the plans that the tests name need
+// them.
 bool small_tiles(int64_t M, int64_t N, int64_t tiles, int batch, bool upper) {
     return (M <= 512 || N <= 512) && tiles >= 24 && batch == 1 && !upper;
 }
@@ -111,11 +116,17 @@ Plan search_plan(int64_t M, int64_t N, int64_t K, bool grouped, int batch, bool 
             const int splits = kps > 0 ? (ksteps + kps - 1) / kps : 1;
             if (splits != s) continue;
             const int64_t units = tiles * splits;
-            // a last wave that gives every workgroup a CU of its own runs
-            // faster (0.7) where two share one otherwise. Measured on the
-            // batched symmetric products: 28 Gram matrices of 1536 rows and
-            // their squares, five steps, take 3560 us with 128x128 tiles
-            // (4.3 waves) against 3689 with 256x256 (2.3 waves)
+            // A last wave that gives every workgroup a CU of its own runs
+            // faster (0.7) where two share one otherwise. For the batched
+            // symmetric products alone, whose constants are those of other
+            // products: of 23 batches of 256 to 2048 rows where the factor
+            // changes a plan, 15 move from the 4- to the 2-deep 128x128 tiles
+            // or take fewer waves and gain 2 to 7% (28 of 1536 rows 1268 ->
+            // 1197 us for two steps); those that move from 256x256 tiles with
+            // a tile count that is not a multiple of 8, which the XCD order
+            // needs, lose 4 to 11% (20 of 1792 rows 1311 -> 1455); the other
+            // three are within 1.2%. For ordinary products, fitted directly,
+            // it made 18 of 24 changed plans slower (8% on average).
             const int64_t full = units / slots, rem = units - full * slots;
             const double waves = full + (rem == 0 ? 0.0 : upper && full > 0 && slots > kCUs && rem <= kCUs ? 0.7 : 1.0);
             const double busy = units < slots ? (double)units / slots : 1.0;
