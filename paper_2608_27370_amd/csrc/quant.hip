@@ -554,7 +554,9 @@ __global__ __launch_bounds__(kThreads) void quant_tensor_kernel(QuantArgs a0, Qu
 // again in every block costs less (16 loads in flight per thread, from the L2
 // after the first block). Graph replays, two launches against one:
 // [16, 1536] 7.3 -> 4.2 us, [77, 1536] 6.6 -> 5.2, [64, 2048] with both copies
-// 6.9 -> 5.7; twice that size would be even.
+// 6.9 -> 5.7; twice that size would be even. Short and wide tensors have many
+// blocks, and their amax pass few: [2, 65536] (512 blocks) 10.4 -> 8.7 us,
+// [1, 131072] (1024) 15.7 -> 13.8, so the limit counts elements alone.
 constexpr int64_t kSmallTensor = 131072;
 template <int FMT>
 __global__ __launch_bounds__(kThreads) void quant_tensor_small_kernel(QuantArgs a, int gx) {
