@@ -100,6 +100,10 @@ bool small_tiles(int64_t M, int64_t N, int64_t tiles, int batch, bool upper) {
 // split, the reduction's launch and the partial sums written and read back.
 Plan search_plan(int64_t M, int64_t N, int64_t K, bool grouped, int batch, bool upper) {
     const int ksteps = (int)((K + kBK - 1) / kBK);
+    // (the factor of block scales was measured where k can be split; with
+    // N % 4 != 0 it cannot, and the element-wise stores of every tile, not
+    // the slices, decide: 3683x5471x896 57 us on 128x128 tiles, 105 on 256x192)
+    const bool scaled = grouped && N % 4 == 0;
     Plan best{0, 1, ksteps};
     double best_cost = -1.0;
     for (int c = 0; c < kNumTiles; ++c) {
@@ -130,7 +134,7 @@ Plan search_plan(int64_t M, int64_t N, int64_t K, bool grouped, int batch, bool 
             const int64_t full = units / slots, rem = units - full * slots;
             const double waves = full + (rem == 0 ? 0.0 : upper && full > 0 && slots > kCUs && rem <= kCUs ? 0.7 : 1.0);
             const double busy = units < slots ? (double)units / slots : 1.0;
-            double cost = waves * (t.fixed_us + t.slice_us * (grouped ? t.grouped : 1.0f) * (kps > 0 ? kps : 1) * (1.0 - 0.378 * (1.0 - busy)));
+            double cost = waves * (t.fixed_us + t.slice_us * (scaled ? t.grouped : 1.0f) * (kps > 0 ? kps : 1) * (1.0 - 0.378 * (1.0 - busy)));
             if (splits > 1) cost += 1.784 + 0.2525e-6 * splits * (double)M * N * 4.0 * batch;
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
