@@ -594,7 +594,10 @@ __global__ __launch_bounds__(kThreads) void quant_tensor_small_kernel(QuantArgs 
 template <int FMT, bool ROWS, bool COLS, bool FLOOR>
 __device__ __forceinline__ void quant_groups_tile(const QuantArgs& a, const Tile& t, int64_t bx, int64_t by,
                                                   const uint32_t w[8][4], uint32_t (*colmax)[kTile / 2], uint8_t* tq) {
-    constexpr bool floor_rule = FLOOR;
+    // (asked at run time in the other rules' instance too: with the careful
+    // path's test folded away the compiler orders the common path's code
+    // otherwise, 2 to 5% slower: [16384, 1536], rows and columns, 20.0 -> 21.0 us)
+    const bool floor_rule = FLOOR || a.pow2 == 2;
 
     if constexpr (ROWS) {
         uint2 c[8];
@@ -614,7 +617,7 @@ __device__ __forceinline__ void quant_groups_tile(const QuantArgs& a, const Tile
                 srow[i] = exp2i(e[i]);
                 c[i] = encode8_pow2<FMT>(w[i], srow[i]);
             }
-        } else if (floor_rule && wave_none(plain.outside())) {
+        } else if (FLOOR && wave_none(plain.outside())) {
             // the floor rule with groups to clip, straight-line too (the
             // groups that need no clipping get the same codes): a branch per
             // group cost the SwiGLU backward's blocks, which take two tiles
@@ -693,7 +696,7 @@ __device__ __forceinline__ void quant_groups_tile(const QuantArgs& a, const Tile
             transpose8x8_b16(w, wt);
 #pragma unroll
             for (int j = 0; j < 8; ++j) ct[j] = encode8_pow2<FMT>(wt[j], scol[j]);
-        } else if (floor_rule && wave_none(plain.outside())) {
+        } else if (FLOOR && wave_none(plain.outside())) {
             uint32_t wt[8][4];
             transpose8x8_b16(w, wt);
 #pragma unroll
@@ -834,9 +837,9 @@ __global__ __launch_bounds__(kThreads) void quant_block_kernel(QuantArgs a) {
     }
 }
 
-// f(floor) with the scale rule as a type: a kernel instance of its own, since
-// the floor rule's clipping path in the other rules' instances cost their
-// small calls 3 to 4% (SwiGLU backward, dH [256, 1024]: 11.6 against 12.1 us).
+// f(floor) with the floor rule as a type: a kernel instance of its own, since
+// its clipping path in the other rules' instances cost their small calls 3 to
+// 4% (SwiGLU backward, dH [256, 1024]: 11.6 against 12.1 us).
 template <class F>
 void by_rule(const QuantArgs& a, F&& f) {
     if (a.pow2 == 2) f(std::true_type{});
